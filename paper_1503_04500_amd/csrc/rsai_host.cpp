@@ -519,8 +519,8 @@ static rsai_status build_impl(int32_t count, const rsai_csc *As, const rsai_para
             // dense class finishes (no more than its record capacity)
             M.capM = n * qmid + std::min<int64_t>(n, big_cap) * (qlast - qmid);
             // the summary, then the states of the build's two single-pass scans (row
-            // pattern, colptr of M), all zeroed by the first launch
-            M.summary = L.take<int64_t>(8 + 5 * MAX2_COPIES / 2 + 2 * scan1_state_elems(n));
+            // pattern; colptr of M in the assembly), all zeroed by the first launch
+            M.summary = L.take<int64_t>(8 + 5 * MAX2_COPIES / 2 + scan1_state_elems(n) + asm_state_elems(n));
             M.scan_state = (unsigned long long *)(M.summary + 8 + 5 * MAX2_COPIES / 2);
             M.colptrM = L.take<int64_t>(n + 1);
             M.rowidxM = L.take<int32_t>(M.capM);
@@ -627,7 +627,8 @@ static rsai_status build_impl(int32_t count, const rsai_csc *As, const rsai_para
                 add(fillpos[i], As[i].n, 0);
                 // the summary (counts the assembly adds up; the adjoint's size maxima,
                 // which rsai_plan_nnz gathers) and the two single-pass scan states
-                add(M.summary, 2 * (8 + 5 * MAX2_COPIES / 2 + 2 * scan1_state_elems(As[i].n)), 0);
+                add(M.summary,
+                    2 * (8 + 5 * MAX2_COPIES / 2 + scan1_state_elems(As[i].n) + asm_state_elems(As[i].n)), 0);
             }
             const int ntab = count <= FILL_TAB ? count : 0;
             for (size_t a = 0; a < fp.size(); a += FILL_SLOTS) {
@@ -823,14 +824,13 @@ static rsai_status build_impl(int32_t count, const rsai_csc *As, const rsai_para
         P->ntiers_used = tlast - t0 + 1 + (big ? 1 + WIDE_LEVELS : 0);
         P->record(3, s);
 
-        // ---- assembly of M per matrix: colptr = scan(nJ), then compaction
+        // ---- assembly of M per matrix: colptr = scan(nJ) and compaction in one launch
         for (int i = 0; i < count; ++i) {
             MatPlan &M = P->mats[i];
             const int64_t n = As[i].n;
-            launch_scan1_i32(P->out.nJ + M.col_base, n, M.colptrM, M.scan_state + scan1_state_elems(n), P->err,
-                             nullptr, s);
             launch_assemble(n, (int)qlast, P->out.off + M.col_base, P->out.nJ + M.col_base, M.colptrM, P->out.arenaJ,
-                            P->out.arenaV, M.rowidxM, M.valM, P->out.status + M.col_base, P->err, M.summary, s);
+                            P->out.arenaV, M.rowidxM, M.valM, P->out.status + M.col_base, P->err,
+                            M.scan_state + scan1_state_elems(n), M.summary, s);
         }
         P->record(4, s);
         hipError_t le = hipGetLastError();

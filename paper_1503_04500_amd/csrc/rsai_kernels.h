@@ -120,10 +120,13 @@ int64_t scan1_state_elems(int64_t n);
 void launch_scan1_i32(const int32_t *in, int64_t n, int64_t *out, unsigned long long *state, int32_t *err,
                       int32_t *host_flags, hipStream_t s);
 
-// ---- assembly: per-column results in the arena -> CSC (rows ascending)
-void launch_assemble(int64_t n, int qcap, const int64_t *off, const int32_t *nJ, const int64_t *colptrM,
+// ---- assembly: per-column results in the arena -> CSC (rows ascending): colptr of M and
+// its entries in one launch (single-pass scan; state: asm_state_elems(n) zeroed words)
+int64_t asm_state_elems(int64_t n);
+void launch_assemble(int64_t n, int qcap, const int64_t *off, const int32_t *nJ, int64_t *colptrM,
                      const int32_t *arenaJ, const double *arenaV, int32_t *rowidxM, double *valM,
-                     const int32_t *status, const int32_t *err, int64_t *summary, hipStream_t s);
+                     const int32_t *status, int32_t *err, unsigned long long *state, int64_t *summary,
+                     hipStream_t s);
 
 // ---- SpMV
 void launch_csc_transpose_fill(int64_t n, const int64_t *colptr, const int32_t *rowidx, const double *val,

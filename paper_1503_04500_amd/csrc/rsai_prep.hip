@@ -323,6 +323,46 @@ __global__ void k_scan_final(const int32_t *in, int64_t n, int64_t nb, const int
 constexpr unsigned long long SC_SUM = 1ull << 62, SC_PRE = 2ull << 62, SC_VAL = (1ull << 62) - 1;
 int64_t scan1_state_elems(int64_t n) { return 1 + (n + SCAN_B - 1) / SCAN_B; }
 
+// Sum of the tiles before `tile`, by its first wave; publishes the tile's sum and prefix.
+// The wave reads 64 predecessors' words at a time (lane i: tile hi - i; a tile before the
+// first counts as a prefix of 0) and sums those up to the nearest prefix; a window with a
+// word not yet written is read again.
+__device__ __forceinline__ int64_t look_back(unsigned long long *w, int64_t tile, int64_t tsum, int32_t *err) {
+    const int lane = threadIdx.x & 63;
+    if (lane == 0 && tile > 0)
+        __hip_atomic_store(&w[tile], SC_SUM | (unsigned long long)tsum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int64_t acc = 0;
+    int64_t hi = tile - 1;
+    unsigned spins = 0;
+    while (hi >= 0) {
+        const int64_t p = hi - lane;
+        const unsigned long long v =
+            p >= 0 ? __hip_atomic_load(&w[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : SC_PRE;
+        const unsigned long long f = v >> 62;
+        const unsigned long long pre = __ballot(f == 2);
+        const int lim = pre ? __ffsll((long long)pre) - 1 : 63;  // lanes 0..lim are needed
+        const unsigned long long need = lim == 63 ? ~0ull : ((2ull << lim) - 1);
+        if (__ballot(f == 0) & need) {
+            if (++spins > (1u << 22)) {
+                if (lane == 0) atomicOr(err, 64);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+            continue;
+        }
+        int64_t x = lane <= lim ? (int64_t)(v & SC_VAL) : 0;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
+        acc += x;
+        if (pre) break;
+        hi -= 64;
+    }
+    if (lane == 0)
+        __hip_atomic_store(&w[tile], SC_PRE | (unsigned long long)(acc + tsum), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    return acc;
+}
+
 __global__ void k_scan1(const int32_t *in, int64_t n, int64_t *out, unsigned long long *state, int32_t *err,
                         int32_t *host_flags) {
     __shared__ int64_t sh[SCAN_T];
@@ -360,44 +400,8 @@ __global__ void k_scan1(const int32_t *in, int64_t n, int64_t *out, unsigned lon
     }
     const int64_t tsum = sh[SCAN_T - 1];
     if (threadIdx.x < 64) {
-        // the first wave reads 64 predecessors' words at a time (lane i: tile hi - i; a
-        // tile before the first counts as a prefix of 0) and sums those up to the
-        // nearest prefix; a window with a word not yet written is read again
-        const int lane = threadIdx.x;
-        unsigned long long *w = state + 1;
-        if (lane == 0 && tile > 0)
-            __hip_atomic_store(&w[tile], SC_SUM | (unsigned long long)tsum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        int64_t acc = 0;
-        int64_t hi = tile - 1;
-        unsigned spins = 0;
-        while (hi >= 0) {
-            const int64_t p = hi - lane;
-            const unsigned long long v =
-                p >= 0 ? __hip_atomic_load(&w[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : SC_PRE;
-            const unsigned long long f = v >> 62;
-            const unsigned long long pre = __ballot(f == 2);
-            const int lim = pre ? __ffsll((long long)pre) - 1 : 63;  // lanes 0..lim are needed
-            const unsigned long long need = lim == 63 ? ~0ull : ((2ull << lim) - 1);
-            if (__ballot(f == 0) & need) {
-                if (++spins > (1u << 22)) {
-                    if (lane == 0) atomicOr(err, 64);
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(1);
-                continue;
-            }
-            int64_t x = lane <= lim ? (int64_t)(v & SC_VAL) : 0;
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
-            acc += x;
-            if (pre) break;
-            hi -= 64;
-        }
-        if (lane == 0) {
-            __hip_atomic_store(&w[tile], SC_PRE | (unsigned long long)(acc + tsum), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-            toff = acc;
-        }
+        const int64_t acc = look_back(state + 1, tile, tsum, err);
+        if (threadIdx.x == 0) toff = acc;
     }
     __syncthreads();
     const int64_t pre = toff + sh[threadIdx.x] - s;
@@ -422,49 +426,122 @@ void launch_scan_i32(const int32_t *in, int64_t n, int64_t *out, int64_t *tmp, h
 }
 
 // ---------------------------------------------------------------- assembly
-// The tier kernels leave each column's (row, value) pairs in ascending row order in
-// its arena slot; assembly is a compaction: one thread per (column, position) pair
-// over n x QCAP, reading the padded slots and writing M at colptrM[k] + t.
+// The size classes leave each column's (row, value) pairs in ascending row order in its
+// arena slot. One launch forms colptr of M (the exclusive scan of nJ) and compacts the
+// slots: a tile of T columns is scanned by its block (single-pass look-back, as in
+// k_scan1) and then copied, 16 lanes per column, 8 columns in flight. Bound by the
+// look-back chain and the copy's latency. Tiles of 256 columns while all tiles fit one
+// look-back window (64 tiles), of 1024 beyond: on the 512 x 512 grid 256 tiles of 1024
+// take 19 us, 1024 tiles of 256 32 us (16 windows); on 1024 columns 10.5 and 8.2 us. As
+// two launches (scan, then copy) these were 26.5 and 12.2 us.
+// state: asm_state_elems(n) zeroed words (k_scan1's layout). The same pass fills the
+// summary the host reads after the build (zeroed at its start): sum[0] = nnz of M,
+// sum[1] = error flags, sum[2..4] = columns with status singular / cap / anything else
+// not ok.
+constexpr int ASM_SMALL = 256, ASM_LARGE = 1024, ASM_WINDOW = 64;
+int64_t asm_state_elems(int64_t n) { return 1 + (n + ASM_SMALL - 1) / ASM_SMALL; }
 
-// 16 lanes per column copy its nJ[k] <= qcap entries from the arena slot into M
-// The same pass fills the summary the host reads after the build (zeroed at its start):
-// out[0] = colptrM[n] (nnz of M), out[1] = error flags, out[2..4] = columns with status
-// singular / cap / anything else not ok.
-__global__ void k_assemble(int64_t n, int qcap, const int64_t *off, const int32_t *nJ, const int64_t *colptrM,
-                           const int32_t *aJ, const double *aV, int32_t *rowidxM, double *valM,
-                           const int32_t *status, const int32_t *err, int64_t *out) {
-    const int64_t total = n * 16;
-    const bool copy = (*err & 64) == 0;  // (no colptr from a scan whose state was not zeroed)
-    int64_t a = 0, b = 0, c = 0;
-    for (int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t k = idx >> 4;
-        const int cnt = copy ? min(nJ[k], qcap) : 0;
-        const int64_t src0 = off[k], dst0 = colptrM[k];
-        for (int t = (int)(idx & 15); t < cnt; t += 16) {
-            rowidxM[dst0 + t] = aJ[src0 + t];
-            valM[dst0 + t] = aV[src0 + t];
-        }
-        if ((idx & 15) == 0) {
-            const int st = status[k];
-            a += (st == 3);
-            b += (st == 6);
-            c += (st != 0 && st != 3 && st != 6);
-        }
+template <int ASM_T>
+__global__ __launch_bounds__(ASM_T) void k_assemble(int64_t n, int qcap, const int64_t *off, const int32_t *nJ,
+                                                    int64_t *colptrM, const int32_t *aJ, const double *aV,
+                                                    int32_t *rowidxM, double *valM, const int32_t *status,
+                                                    int32_t *err, unsigned long long *state, int64_t *sum) {
+    __shared__ int loc[ASM_T + 1];  // offsets of the tile's columns in the tile
+    __shared__ int64_t src[ASM_T];
+    __shared__ int wsum[ASM_T / 64];
+    __shared__ int64_t toff;
+    __shared__ unsigned long long tk;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (tid == 0) tk = atomicAdd(&state[0], 1ull);
+    __syncthreads();
+    const int64_t nb = (n + ASM_T - 1) / ASM_T;
+    const int64_t tile = (int64_t)tk;
+    if (tile >= nb) {
+        if (tid == 0) atomicOr(err, 64);
+        return;
     }
-    if (a) atomicAdd((unsigned long long *)&out[2], (unsigned long long)a);
-    if (b) atomicAdd((unsigned long long *)&out[3], (unsigned long long)b);
-    if (c) atomicAdd((unsigned long long *)&out[4], (unsigned long long)c);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        out[0] = colptrM[n];
-        out[1] = *err;
+    const int64_t k = tile * ASM_T + tid;
+    const int cnt = k < n ? nJ[k] : 0;
+    src[tid] = k < n ? off[k] : 0;
+    const int st = k < n ? status[k] : 0;
+    // columns that did not finish: one atomic per wave and kind that occurs
+    const unsigned long long b3 = __ballot(st == 3), b6 = __ballot(st == 6), bx = __ballot(st != 0 && st != 3 && st != 6);
+    if (lane == 0) {
+        if (b3) atomicAdd((unsigned long long *)&sum[2], (unsigned long long)__popcll(b3));
+        if (b6) atomicAdd((unsigned long long *)&sum[3], (unsigned long long)__popcll(b6));
+        if (bx) atomicAdd((unsigned long long *)&sum[4], (unsigned long long)__popcll(bx));
+    }
+    int x = cnt;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(x, d);
+        if (lane >= d) x += y;
+    }
+    if (lane == 63) wsum[w] = x;
+    __syncthreads();
+    int before = 0, tsum = 0;
+#pragma unroll
+    for (int u = 0; u < ASM_T / 64; ++u) {
+        if (u < w) before += wsum[u];
+        tsum += wsum[u];
+    }
+    loc[tid] = before + x - cnt;
+    if (tid == 0) loc[ASM_T] = tsum;
+    if (w == 0) {
+        const int64_t acc = look_back(state + 1, tile, tsum, err);
+        if (lane == 0) toff = acc;
+    }
+    __syncthreads();
+    const int64_t base = toff;
+    if (k < n) colptrM[k] = base + loc[tid];
+    if (tile == nb - 1 && tid == 0) {
+        colptrM[n] = base + tsum;
+        sum[0] = base + tsum;
+        sum[1] = __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // (no copy of columns that the CSC check or a class left unwritten: their count is 0)
+    // U columns of a 16-lane group at a time, their first 16 entries loaded together
+    constexpr int U = 8;
+    const int gl = tid & 15;
+    for (int c0 = tid >> 4; c0 < ASM_T; c0 += U * (ASM_T / 16)) {
+        int j[U], len[U];
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c = c0 + u * (ASM_T / 16);
+            len[u] = min(loc[c + 1] - loc[c], qcap);
+            j[u] = 0;
+            v[u] = 0.0;
+            if (gl < len[u]) {
+                j[u] = aJ[src[c] + gl];
+                v[u] = aV[src[c] + gl];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c = c0 + u * (ASM_T / 16);
+            const int64_t d0 = base + loc[c];
+            if (gl < len[u]) {
+                rowidxM[d0 + gl] = j[u];
+                valM[d0 + gl] = v[u];
+            }
+            for (int t = gl + 16; t < len[u]; t += 16) {
+                rowidxM[d0 + t] = aJ[src[c] + t];
+                valM[d0 + t] = aV[src[c] + t];
+            }
+        }
     }
 }
-void launch_assemble(int64_t n, int qcap, const int64_t *off, const int32_t *nJ, const int64_t *colptrM,
+void launch_assemble(int64_t n, int qcap, const int64_t *off, const int32_t *nJ, int64_t *colptrM,
                      const int32_t *arenaJ, const double *arenaV, int32_t *rowidxM, double *valM,
-                     const int32_t *status, const int32_t *err, int64_t *summary, hipStream_t s) {
-    hipLaunchKernelGGL(k_assemble, dim3(nblocks(n * 16, 1024)), dim3(256), 0, s, n, qcap, off, nJ, colptrM,
-                       arenaJ, arenaV, rowidxM, valM, status, err, summary);
+                     const int32_t *status, int32_t *err, unsigned long long *state, int64_t *summary,
+                     hipStream_t s) {
+    auto go = [&](auto kernel, int64_t t) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((n + t - 1) / t)), dim3((unsigned)t), 0, s, n, qcap, off, nJ, colptrM,
+                           arenaJ, arenaV, rowidxM, valM, status, err, state, summary);
+    };
+    if (n <= (int64_t)ASM_SMALL * ASM_WINDOW) go(k_assemble<ASM_SMALL>, ASM_SMALL);
+    else go(k_assemble<ASM_LARGE>, ASM_LARGE);
 }
 
 // ---------------------------------------------------------------- SpMV
