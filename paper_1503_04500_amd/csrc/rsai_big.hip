@@ -1,7 +1,7 @@
-// Large size class of the RSAI(tol) build: one 256-thread workgroup per column,
-// for the columns that outgrow the register tiers (tall LS blocks A(I_k, J_k) of up
-// to BMMAX rows and BQMAX columns, e.g. the power-law matrices whose long columns
-// bring hundreds to thousands of rows into I_k).
+// Second level of the dense class of the RSAI(tol) build: one 256-thread workgroup per
+// column, for the columns that outgrow the first level (rsai_dense.hip): LS blocks
+// A(I_k, J_k) of up to BMMAX rows and BQMAX columns, e.g. the power-law matrices whose
+// long columns bring hundreds to thousands of rows into I_k.
 //
 // Same steps as the register tiers (Algorithm 1 with the dropping of Section 4):
 //   * index sets are LDS hash sets; new rows are numbered in ascending global order
@@ -14,8 +14,8 @@
 //   * the residual for step 4 is A(I,J) m - e_k(I) accumulated from the sparse
 //     columns in ascending column order (eq. (2.4)), so exact ties reach the
 //     smaller-index rule.
-// Columns arrive as spill records of the previous class; a column that outgrows this
-// class ends with status RSAI_E_CAP.
+// Columns arrive as spill records in the dense class's queue, this level's listed by
+// their queue positions; a column that outgrows it ends with status RSAI_E_CAP.
 #include <climits>
 #include <utility>
 
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(NT) void big_kernel(BigArgs args) {
     const int tid = threadIdx.x;
     if (*args.err & ERR_SKIP) return;
     const BuildParams P = args.P;
-    const int64_t Q = min((int64_t)(*args.rec_in_count), args.rec_in_cap);
+    const int Q = *args.list_count;
     double *B = args.scratch + (int64_t)blockIdx.x * args.scratch_stride;  // [BQMAX][BMMAX]
     const int64_t ld = args.ld;                                            // rows per block column
     double *y = B + (int64_t)BQMAX_BIG * ld;                               // Q^T e
@@ -359,7 +359,8 @@ __global__ __launch_bounds__(NT) void big_kernel(BigArgs args) {
     unsigned char *rfl = reinterpret_cast<unsigned char *>(Il + ld);       // row in R
     double *gred = racc + ld + (ld * 5 + 7) / 8 + 8;                       // panel partials
 
-    for (int64_t pos = blockIdx.x; pos < Q; pos += gridDim.x) {
+    for (int at = blockIdx.x; at < Q; at += gridDim.x) {
+        const int64_t pos = args.list[at];
         const int32_t *rec = args.rec_in + pos * (int64_t)args.rec_in_stride;
         const int ucol = rec[0], mat = rec[1], k = rec[2];
         int l = rec[3], q = rec[4], m = rec[5];

@@ -151,7 +151,8 @@ struct rsai_plan {
     ColOut out{};
     int64_t arena_cap = 0;
     int32_t *rec[8] = {};
-    double *big_scratch = nullptr;   // per-workgroup slabs of the large size class
+    double *big_scratch = nullptr;   // per-workgroup slabs of the dense class's second level
+    int32_t *big_list = nullptr;     // its columns: positions in the dense class's queue
     int32_t *rec_count = nullptr;
     int32_t *err = nullptr;
     unsigned long long *stats = nullptr;
@@ -481,6 +482,7 @@ static rsai_status build_impl(int32_t count, const rsai_csc *As, const rsai_para
     // feeds class t0 + 1 + k), then the workgroup classes' queues. Plain: two queues
     // used in turn by the loop launches (counter L is written by launch L), the queue of
     // the columns that outgrow the register class, then the workgroup classes' queues.
+    // The counter past the last one is the dense class's second level's.
     const int nlaunch = plain ? P->p.lmax + 2 + WIDE_LEVELS : (tlast - t0 + 1 + (big ? 1 + WIDE_LEVELS : 0));
     const int q_in0 = plain ? 2 : tlast;                      // rec[] of sparse-block level 0's input
     const int c_in0 = plain ? P->p.lmax + 1 : tlast - t0;     // its counter
@@ -562,6 +564,7 @@ static rsai_status build_impl(int32_t count, const rsai_csc *As, const rsai_para
         if (big)
             for (int w = 0; w < WIDE_LEVELS; ++w)
                 P->rec[q_wide + w] = L.take<int32_t>(wide_rec_cap[w] * (int64_t)wide_queue_stride(w));
+        P->big_list = L.take<int32_t>(big_cap);
         P->big_scratch = big ? L.take<double>((int64_t)big_blocks * big_scratch_stride(big_ld)) : nullptr;
     };
     Layout L0;
@@ -760,6 +763,7 @@ static rsai_status build_impl(int32_t count, const rsai_csc *As, const rsai_para
             // first on the compressed block, then (rarely) on the dense block.
             // Queue w (rec[q_wide + w], counter c_wide + w) feeds level w + 1; the
             // last one the dense class
+            int32_t *dense_count = nullptr;
             auto queue = [&](int w, int32_t *&buf, int &stride, int32_t *&count, int64_t &cap) {
                 buf = P->rec[q_wide + w];
                 stride = wide_queue_stride(w);
@@ -806,15 +810,28 @@ static rsai_status build_impl(int32_t count, const rsai_csc *As, const rsai_para
                 w.err = P->err;
                 launch_wide_kernel(lv, w, device_cus() * wide_blocks_per_cu(lv), s);
             }
+            // the dense class: its first level reads the queue and lists the columns that
+            // do not fit it (at most one entry per record) for the second
+            DenseArgs d{};
+            d.mats = P->d_mats;
+            d.P = base.P;
+            d.out = P->out;
+            d.arena_base = big_base;
+            queue(WIDE_LEVELS - 1, d.rec, d.rec_stride, dense_count, d.rec_cap);
+            d.rec_count = dense_count;
+            d.next_list = P->big_list;
+            d.next_count = P->rec_count + nlaunch;
+            d.err = P->err;
+            launch_dense_kernel(d, (int)std::min<int64_t>(d.rec_cap, (int64_t)cus * dense_blocks_per_cu()), s);
             BigArgs b{};
             b.mats = P->d_mats;
             b.P = base.P;
             b.out = P->out;
             b.arena_base = big_base;
-            b.rec_in = P->rec[q_wide + WIDE_LEVELS - 1];
-            b.rec_in_stride = wide_queue_stride(WIDE_LEVELS - 1);
-            b.rec_in_count = P->rec_count + (c_wide + WIDE_LEVELS - 1);
-            b.rec_in_cap = wide_rec_cap[WIDE_LEVELS - 1];
+            b.rec_in = d.rec;
+            b.rec_in_stride = d.rec_stride;
+            b.list = P->big_list;
+            b.list_count = d.next_count;
             b.scratch = P->big_scratch;
             b.scratch_stride = big_scratch_stride(big_ld);
             b.ld = big_ld;

@@ -59,7 +59,28 @@ int wide_queue_stride(int queue);
 int wide_blocks_per_cu(int level);
 void launch_wide_kernel(int level, const WideArgs &a, int blocks, hipStream_t s);
 
-// ---- large size class (rsai_big.hip): one workgroup per column
+// ---- dense class, first level (rsai_dense.hip): one workgroup per column, the block in
+// registers. Reads the dense class's queue; a column past its limits stays in its record
+// and its queue position goes to the second level's list.
+constexpr int DENSE_MMAX = 128;  // rows of the LS block
+constexpr int DENSE_QMAX = 63;   // columns of the LS block
+struct DenseArgs {
+    const MatDev *mats;
+    BuildParams P;
+    ColOut out;
+    int64_t arena_base;       // slot of the record at queue position pos: arena_base + pos * BQMAX_BIG
+    int32_t *rec;             // records (rewritten in place for the second level)
+    int rec_stride;
+    const int32_t *rec_count;
+    int64_t rec_cap;
+    int32_t *next_list;       // queue positions for the second level
+    int32_t *next_count;
+    int32_t *err;
+};
+int dense_blocks_per_cu();
+void launch_dense_kernel(const DenseArgs &a, int blocks, hipStream_t s);
+
+// ---- dense class, second level (rsai_big.hip): one workgroup per column
 constexpr int BMMAX_BIG = 8192;  // rows of the LS block
 constexpr int BQMAX_BIG = 128;   // columns of the LS block
 struct BigArgs {
@@ -67,10 +88,10 @@ struct BigArgs {
     BuildParams P;
     ColOut out;
     int64_t arena_base;       // slot of the record at queue position pos: arena_base + pos * BQMAX_BIG
-    const int32_t *rec_in;
+    const int32_t *rec_in;    // records of the dense class's queue
     int rec_in_stride;
-    const int32_t *rec_in_count;
-    int64_t rec_in_cap;
+    const int32_t *list;      // the queue positions of this level's columns
+    const int32_t *list_count;
     double *scratch;          // per-workgroup slabs
     int64_t scratch_stride;   // doubles per slab
     int64_t ld;               // rows per block column in the slab: min(BMMAX_BIG, largest n)
