@@ -257,19 +257,16 @@ __global__ __launch_bounds__(64) void backward_kernel(BwdArgs a) {
         for (int j = 0; j < QMAX; ++j) {
             if (j >= qmaxw) continue;
             const bool ja = act && j < q;
-            double s2 = 0.0, x0p = 0.0;
+            double s2 = 0.0;
 #pragma unroll
-            for (int r = 0; r < RPL; ++r) {
-                const int i = r * G + gl;
-                if (i >= j) s2 += b[r][j] * b[r][j];
-                if (i == j) x0p = b[r][j];
-            }
+            for (int r = 0; r < RPL; ++r)
+                if (r * G + gl >= j) s2 += b[r][j] * b[r][j];
             s2 = gsum<G>(s2);
-            const double x0 = gsum<G>(x0p);
-            const double nx = sqrt(s2);
+            const double x0 = bcast_lane<G>(b[j / G][j], j % G);
+            double nx, bj;
+            hh_scalars(s2, x0, nx, bj);
             const double alpha = (x0 >= 0.0) ? -nx : nx;
             const double vj = x0 - alpha;
-            const double bj = (nx > 0.0) ? 1.0 / (nx * (nx + fabs(x0))) : 0.0;
             if (ja) {
 #pragma unroll
                 for (int r = 0; r < RPL; ++r)

@@ -269,10 +269,10 @@ __device__ __forceinline__ void panel_step(double (&pv)[RPT][NB], int m, int p0,
     }
     bsum_many<0, 2>(x, S);
     const double x0 = x[1];
-    const double nx = sqrt(x[0]);
+    double nx, be;
+    hh_scalars(x[0], x0, nx, be);
     const double alpha = (x0 >= 0.0) ? -nx : nx;
     const double vj = x0 - alpha;
-    const double be = (nx > 0.0) ? 1.0 / (nx * (nx + fabs(x0))) : 0.0;
     if (!(nx > 0.0)) singular = true;
     double v[RPT];
 #pragma unroll

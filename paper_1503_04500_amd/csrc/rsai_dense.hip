@@ -73,12 +73,6 @@ struct DLds {
     unsigned char rfl[MM];     // row in R (used dominant rows)
 };
 
-__device__ __forceinline__ double readlane_f64(double x, int l) {
-    const long long b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffLL), l);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
 // The matrix, read through a pointer whose value the compiler cannot see: its pointers
 // are loaded where a phase uses them instead of being held in scalar registers across
 // the solve.
@@ -223,8 +217,7 @@ __device__ __forceinline__ double factor_solve(double (&b)[NS], int top, int qn,
         for (int j = qn - 1; j >= 0; --j) {
             const double rj = (lane < j) ? S.R[rcol(j) + lane] : 0.0;
             const double yj = readlane_f64(y, j), ri = readlane_f64(ril, j);
-            double mj = yj * ri;
-            mj = __builtin_fma(__builtin_fma(-mj, readlane_f64(rdl, j), yj), ri, mj);
+            const double mj = div_by(yj, readlane_f64(rdl, j), ri);
             if (lane == j) mine = mj;
             y -= rj * mj;
         }

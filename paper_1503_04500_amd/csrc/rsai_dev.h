@@ -225,6 +225,70 @@ __device__ __forceinline__ int gbcast_i(int x, bool is_src) {
     return gsum_i<G>(is_src ? x : 0);
 }
 
+// Value of x held by lane l of the group, in every lane; l is a constant once the caller's
+// loop is unrolled. 16 lanes: one row_newbcast move per word; 8 lanes: one per word and
+// half row (the bank mask picks the half it writes); 64 lanes: a lane read.
+template <int G, int L>
+__device__ __forceinline__ int bcast_lane_i32(int x) {
+    if constexpr (G == 16) {
+        return __builtin_amdgcn_update_dpp(x, x, 0x150 + L, 0xF, 0xF, true);
+    } else {
+        static_assert(G == 8, "group size");
+        const int lo = __builtin_amdgcn_update_dpp(x, x, 0x150 + L, 0xF, 0x3, true);
+        return __builtin_amdgcn_update_dpp(lo, x, 0x150 + 8 + L, 0xF, 0xC, true);
+    }
+}
+template <int G, int L>
+__device__ __forceinline__ double bcast_lane_at(double x) {
+    const long long b = __double_as_longlong(x);
+    const int lo = bcast_lane_i32<G, L>((int)(b & 0xffffffffLL));
+    const int hi = bcast_lane_i32<G, L>((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+__device__ __forceinline__ double readlane_f64(double x, int l) {
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffLL), l);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+template <int G>
+__device__ __forceinline__ double bcast_lane(double x, int l) {
+    if constexpr (G == 64) {
+        return readlane_f64(x, l);
+    } else {
+        switch (l) {
+            case 0: return bcast_lane_at<G, 0>(x);
+            case 1: return bcast_lane_at<G, 1>(x);
+            case 2: return bcast_lane_at<G, 2>(x);
+            case 3: return bcast_lane_at<G, 3>(x);
+            case 4: return bcast_lane_at<G, 4>(x);
+            case 5: return bcast_lane_at<G, 5>(x);
+            case 6: return bcast_lane_at<G, 6>(x);
+            case 7: return bcast_lane_at<G, 7>(x);
+            default: break;
+        }
+        if constexpr (G == 16) {
+            switch (l) {
+                case 8: return bcast_lane_at<G, 8>(x);
+                case 9: return bcast_lane_at<G, 9>(x);
+                case 10: return bcast_lane_at<G, 10>(x);
+                case 11: return bcast_lane_at<G, 11>(x);
+                case 12: return bcast_lane_at<G, 12>(x);
+                case 13: return bcast_lane_at<G, 13>(x);
+                case 14: return bcast_lane_at<G, 14>(x);
+                default: return bcast_lane_at<G, 15>(x);
+            }
+        }
+        return x;
+    }
+}
+// a / b from r = 1 / b: the product corrected by its residual (the quotient's error stays
+// within a rounding of the division's)
+__device__ __forceinline__ double div_by(double a, double b, double r) {
+    const double q = a * r;
+    return __builtin_fma(__builtin_fma(-q, b, a), r, q);
+}
+
 // Wave-wide max of an int (all 64 lanes): row reduction then 4 lane reads.
 __device__ __forceinline__ int wave_max_i(int x) {
     x = gmax_i<16>(x);

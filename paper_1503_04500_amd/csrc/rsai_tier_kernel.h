@@ -84,6 +84,8 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
 #pragma unroll
     for (int r = 0; r < RPL; ++r) {
         y[r] = 0.0;
+        rd[r] = 1.0;
+        bt[r] = 0.0;
 #pragma unroll
         for (int c = 0; c < QMAX; ++c) b[r][c] = 0.0;
     }
@@ -578,21 +580,17 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
 #pragma unroll
                 for (int r = 0; r < RPL; ++r) vr[r] = (r * G + gl >= j) ? b[r][j] : 0.0;
                 if (j < qloww) {
-                    bj = gsum<G>((gl == j % G) ? bt[j / G] : 0.0);
+                    bj = bcast_lane<G>(bt[j / G], j % G);
                 } else {
-                    double s2 = 0.0, x0p = 0.0;
+                    double s2 = 0.0;
 #pragma unroll
-                    for (int r = 0; r < RPL; ++r) {
-                        const int i = r * G + gl;
-                        s2 += vr[r] * vr[r];
-                        if (i == j) x0p = b[r][j];
-                    }
+                    for (int r = 0; r < RPL; ++r) s2 += vr[r] * vr[r];
                     s2 = gsum<G>(s2);
-                    const double x0 = gsum<G>(x0p);
-                    const double nx = sqrt(s2);
+                    const double x0 = bcast_lane<G>(b[j / G][j], j % G);
+                    double nx, bnew;
+                    hh_scalars(s2, x0, nx, bnew);
                     const double alpha = (x0 >= 0.0) ? -nx : nx;
                     const double vj = x0 - alpha;
-                    const double bnew = (nx > 0.0) ? 1.0 / (nx * (nx + fabs(x0))) : 0.0;
                     if (ja && newr) {
                         if (!(nx > 0.0)) singular = true;
 #pragma unroll
@@ -609,7 +607,7 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
                             }
                     }
                     double bold = 0.0;
-                    if (wave_any(ja && !newr)) bold = gsum<G>((gl == j % G) ? bt[j / G] : 0.0);
+                    if (wave_any(ja && !newr)) bold = bcast_lane<G>(bt[j / G], j % G);
                     bj = newr ? bnew : bold;
                 }
                 // the columns right of j in chunks of QCB: the chunk's products and
@@ -658,19 +656,18 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
             }
             // ---- back substitution R m = (Q^T e)(0:qn)
             {
-                double z[RPL];
+                // (every lane divides by the diagonal of its rows; the group takes the owner's)
+                double z[RPL], ri[RPL];
 #pragma unroll
-                for (int r = 0; r < RPL; ++r) z[r] = y[r];
+                for (int r = 0; r < RPL; ++r) {
+                    z[r] = y[r];
+                    ri[r] = 1.0 / rd[r];
+                }
 #pragma unroll
                 for (int j = QMAX - 1; j >= 0; --j) {
                     if (j >= qmaxw) continue;
                     const bool ja = act && j < qn;
-                    constexpr int dummy = 0;
-                    (void)dummy;
-                    const bool own = (gl == j % G);
-                    double val = 0.0;
-                    if (own && ja) val = z[j / G] / rd[j / G];
-                    const double mj = gsum<G>(val);
+                    const double mj = bcast_lane<G>(div_by(z[j / G], rd[j / G], ri[j / G]), j % G);
                     if (ja) {
                         if (gl == 0) S.mt[j] = mj;
 #pragma unroll

@@ -94,13 +94,6 @@ __device__ __forceinline__ double wsum(double x) {
     return x;
 }
 
-__device__ __forceinline__ double readlane_f64(double x, int l) {
-    const long long b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffLL), l);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-
 // (a desc, g asc) order of dominant-row candidates
 __device__ __forceinline__ bool better(double a, int g, double b, int h) { return a > b || (a == b && g < h); }
 
@@ -540,9 +533,9 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                                 s0 += u[t] * u[t];
                                 s1 += u[t + 1] * u[t + 1];
                             }
-                            const double nx = sqrt(s0 + s1);
+                            double nx, be;
+                            hh_scalars(s0 + s1, x0, nx, be);
                             const double alpha = (x0 >= 0.0) ? -nx : nx;
-                            const double be = (nx > 0.0) ? 1.0 / (nx * (nx + fabs(x0))) : 0.0;
                             const double v0 = x0 - alpha;
                             if (!(nx > 0.0)) singular = true;
                             if (lane > j && lane <= q) {
@@ -599,9 +592,9 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                             }
                             s += wsum(r);
                         }
-                        const double nx = sqrt(s);
+                        double nx, be;
+                        hh_scalars(s, x0, nx, be);
                         const double alpha = (x0 >= 0.0) ? -nx : nx;
-                        const double be = (nx > 0.0) ? 1.0 / (nx * (nx + fabs(x0))) : 0.0;
                         const double v0 = x0 - alpha;
                         if (!(nx > 0.0)) singular = true;
                         if (act) {
@@ -634,16 +627,19 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                     wave_sync();
                     if (!singular) {
                         // back substitution: lane i holds (Q^T e)_i; m_j broadcast by readlane
+                        // (the divisions by the diagonal done beforehand, a lane each)
                         double y = (lane < q) ? S.blk[lane * ld + q] : 0.0;
+                        const double rdl = (lane < q) ? S.rd[lane] : 1.0;
+                        const double ril = 1.0 / rdl;
+                        double mine = 0.0;
                         for (int j = q - 1; j >= 0; --j) {
-                            const long long yb = __double_as_longlong(y);
-                            const int lo = __builtin_amdgcn_readlane((int)(yb & 0xffffffffLL), j);
-                            const int hi = __builtin_amdgcn_readlane((int)(yb >> 32), j);
-                            const double yj = __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-                            const double mj = yj / S.rd[j];
-                            if (lane == 0) S.mt[j] = mj;
-                            if (lane < j) y -= S.blk[lane * ld + j] * mj;
+                            const double rj = (lane < j) ? S.blk[lane * ld + j] : 0.0;
+                            const double mj =
+                                div_by(readlane_f64(y, j), readlane_f64(rdl, j), readlane_f64(ril, j));
+                            if (lane == j) mine = mj;
+                            y -= rj * mj;
                         }
+                        if (lane < q) S.mt[lane] = mine;
                     } else if (lane == 0) {
                         S.flag = 1;
                     }
