@@ -89,13 +89,13 @@ struct TierArgs {
 // the new-entry lists and segment tables of the augmentation phases, and the
 // residual accumulator and column order of the dominant-row phase.
 template <class C>
-struct GLds {
+struct alignas(16) GLds {
     double stage[C::STAGE * C::MMAX];
     double mt[C::QMAX];       // solution of the last LS solve, by column slot
     int64_t cb[C::QMAX];      // first entry of the column in each slot of J (CSC of A)
     int cl[C::QMAX];          // its length
     int Ilist[C::MMAX];
-    int Jlist[C::QMAX];
+    alignas(16) int Jlist[C::QMAX + 4];  // (three entries of INT_MAX after the last column)
     int hI[C::HSI];
     int hJ[C::HSJ];
     int Rh[CMAX];             // pending dominant rows
@@ -105,15 +105,16 @@ struct GLds {
     unsigned char hIv[C::HSI];  // local row of each key in hI
 
     // augmentation phases (K, C, D)
+    static constexpr int NEWP = (C::NEWC + 4 + 3) / 4 * 4;  // keys with room for the padding
     __device__ int *newk() { return reinterpret_cast<int *>(stage); }
-    __device__ int *news() { return newk() + C::NEWC; }
-    __device__ int64_t *segb() { return reinterpret_cast<int64_t *>(stage + C::NEWC); }
+    __device__ int *news() { return newk() + NEWP; }
+    __device__ int64_t *segb() { return reinterpret_cast<int64_t *>(stage + NEWP); }
     __device__ int *pref() { return reinterpret_cast<int *>(segb() + C::QMAX); }
     // dominant-row phase (J)
     __device__ double *racc() { return stage; }
     __device__ int *ord() { return reinterpret_cast<int *>(stage + C::MMAX); }
 
-    static_assert(C::NEWC * 8 + C::QMAX * 8 + C::PREF * 4 <= C::STAGE * C::MMAX * 8, "scratch fits the tile");
+    static_assert(NEWP * 8 + C::QMAX * 8 + C::PREF * 4 <= C::STAGE * C::MMAX * 8, "scratch fits the tile");
     static_assert(C::MMAX * 8 + C::QMAX * 4 <= C::STAGE * C::MMAX * 8, "scratch fits the tile");
     static_assert(C::MMAX < 256, "local rows fit a byte");
 };

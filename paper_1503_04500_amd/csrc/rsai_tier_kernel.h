@@ -270,17 +270,17 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
                 wave_sync();
             }
             const int nnew = (doK && !ovf) ? S.cnt : 0;
+            if (nnew > 0 && gl < 4) S.newk()[nnew + gl] = INT_MAX;
+            wave_sync();
             if (doK) {
+                constexpr int NJ = (QMAX + G - 1) / G;
+                int key[NJ], rank[NJ];
 #pragma unroll
-                for (int s = 0; s < NNEW; ++s) {
-                    int idx = s * G + gl;
-                    if (idx < nnew) {
-                        int key = S.newk()[idx];
-                        int rank = 0;
-                        for (int t = 0; t < nnew; ++t) rank += (S.newk()[t] < key) ? 1 : 0;
-                        S.Jlist[q + rank] = key;
-                    }
-                }
+                for (int s = 0; s < NJ; ++s) key[s] = (s * G + gl < nnew) ? S.newk()[s * G + gl] : INT_MIN;
+                ranks_in<NJ>(S.newk(), nnew, key, rank);
+#pragma unroll
+                for (int s = 0; s < NJ; ++s)
+                    if (s * G + gl < nnew) S.Jlist[q + rank[s]] = key[s];
                 if (linc) ++l;  // step 6
                 if (ovf) {
                     spill = true;
@@ -376,18 +376,20 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
             // ============================ D. number the new rows (ascending order)
             const int nnew = (doC && !ovf) ? S.cnt : 0;
             int kpos = -1;
-            if (doC && !ovf) {
+            if (nnew > 0 && gl < 4) S.newk()[nnew + gl] = INT_MAX;
+            wave_sync();
+            if (nnew > 0) {
+                int key[NNEW], rank[NNEW];
+#pragma unroll
+                for (int s = 0; s < NNEW; ++s) key[s] = (s * G + gl < nnew) ? S.newk()[s * G + gl] : INT_MIN;
+                ranks_in<NNEW>(S.newk(), nnew, key, rank);
 #pragma unroll
                 for (int s = 0; s < NNEW; ++s) {
-                    int idx = s * G + gl;
-                    if (idx < nnew) {
-                        int key = S.newk()[idx];
-                        int rank = 0;
-                        for (int t = 0; t < nnew; ++t) rank += (S.newk()[t] < key) ? 1 : 0;
-                        int li = m + rank;
-                        S.Ilist[li] = key;
-                        S.hIv[S.news()[idx]] = li;
-                        if (key == k) kpos = li;
+                    if (s * G + gl < nnew) {
+                        const int li = m + rank[s];
+                        S.Ilist[li] = key[s];
+                        S.hIv[S.news()[s * G + gl]] = li;
+                        if (key[s] == k) kpos = li;
                     }
                 }
             }
@@ -610,6 +612,10 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
                     if (wave_any(ja && !newr)) bold = bcast_lane<G>(bt[j / G], j % G);
                     bj = newr ? bnew : bold;
                 }
+                // groups that do not take part have f = 0 below (as have the zero columns
+                // past qn), and the columns a stored reflector must leave: no lane masks
+                bj = ja ? bj : 0.0;
+                const int lo = newr ? 0 : qlo;
                 // the columns right of j in chunks of QCB: the chunk's products and
                 // group sums are independent chains the wave issues interleaved
 #pragma unroll
@@ -633,12 +639,9 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
                     for (int u = 0; u < QCB; ++u) {
                         const int c = c0 + u;
                         if (c > j && c < QMAX) {
-                            const bool ca = ja && c < qn && (newr || c >= qlo);
-                            if (ca) {
-                                const double f = bj * w[u];
+                            const double f = (c >= lo) ? bj * w[u] : 0.0;
 #pragma unroll
-                                for (int r = 0; r < RPL; ++r) b[r][c] -= f * vr[r];
-                            }
+                            for (int r = 0; r < RPL; ++r) b[r][c] -= f * vr[r];
                         }
                     }
                 }
@@ -647,11 +650,9 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
 #pragma unroll
                     for (int r = 0; r < RPL; ++r) w += vr[r] * y[r];
                     w = gsum<G>(w);
-                    if (ja && newr) {
-                        const double f = bj * w;
+                    const double f = newr ? bj * w : 0.0;
 #pragma unroll
-                        for (int r = 0; r < RPL; ++r) y[r] -= f * vr[r];
-                    }
+                    for (int r = 0; r < RPL; ++r) y[r] -= f * vr[r];
                 }
             }
             // ---- back substitution R m = (Q^T e)(0:qn)
@@ -667,14 +668,15 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
                 for (int j = QMAX - 1; j >= 0; --j) {
                     if (j >= qmaxw) continue;
                     const bool ja = act && j < qn;
-                    const double mj = bcast_lane<G>(div_by(z[j / G], rd[j / G], ri[j / G]), j % G);
-                    if (ja) {
-                        if (gl == 0) S.mt[j] = mj;
+                    double mj = bcast_lane<G>(div_by(z[j / G], rd[j / G], ri[j / G]), j % G);
+                    mj = ja ? mj : 0.0;
 #pragma unroll
-                        for (int r = 0; r < RPL; ++r)
-                            if (r * G + gl < j) z[r] -= b[r][j] * mj;
-                    }
+                    for (int r = 0; r < RPL; ++r) z[r] -= (r * G + gl < j ? b[r][j] : 0.0) * mj;
                 }
+                // (row j of z is final once step j has taken it)
+#pragma unroll
+                for (int r = 0; r < RPL; ++r)
+                    if (act && r * G + gl < qn) S.mt[r * G + gl] = div_by(z[r], rd[r], ri[r]);
             }
             // ---- residual norm ||(Q^T e)(qn:m)||, plus r(k) = -1 if k is not in I
             {
@@ -777,17 +779,17 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
             double *racc = S.racc();           // [MMAX] accumulator
             const double *mts = S.mt;          // [QMAX] solution values by slot
             int *ord = S.ord();                // [QMAX] slots in ascending column order
+            if (sel && gl < 4) S.Jlist[q + gl] = INT_MAX;
+            wave_sync();
             if (sel) {
+                constexpr int NJ = (QMAX + G - 1) / G;
+                int key[NJ], rank[NJ];
 #pragma unroll
-                for (int s = 0; s < (QMAX + G - 1) / G; ++s) {
-                    const int c = s * G + gl;
-                    if (c < q) {
-                        const int jc = S.Jlist[c];
-                        int rank = 0;
-                        for (int t = 0; t < q; ++t) rank += (S.Jlist[t] < jc) ? 1 : 0;
-                        ord[rank] = c;
-                    }
-                }
+                for (int s = 0; s < NJ; ++s) key[s] = (s * G + gl < q) ? S.Jlist[s * G + gl] : INT_MIN;
+                ranks_in<NJ>(S.Jlist, q, key, rank);
+#pragma unroll
+                for (int s = 0; s < NJ; ++s)
+                    if (s * G + gl < q) ord[rank[s]] = s * G + gl;
 #pragma unroll
                 for (int r = 0; r < RPL; ++r) racc[r * G + gl] = 0.0;
             }
@@ -897,20 +899,24 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
         }
 
         // ================================================== output of a column
+        if (finish && gl < 4) S.Jlist[q + gl] = INT_MAX;
+        wave_sync();
         if (finish) {
             const int64_t slot = kargs()->arena_base + ucol * (int64_t)QMAX;
             const int qq = (status == ST_OK) ? q : 0;
             // m_k with its rows in ascending order (rank of each entry in the group)
+            {
+                constexpr int NJ = (QMAX + G - 1) / G;
+                int key[NJ], rank[NJ];
 #pragma unroll
-            for (int s = 0; s < (QMAX + G - 1) / G; ++s) {
-                const int c = s * G + gl;
-                if (c < qq) {
-                    const int jc = S.Jlist[c];
-                    int rank = 0;
-                    for (int t = 0; t < qq; ++t) rank += (S.Jlist[t] < jc) ? 1 : 0;
-                    kargs()->out.arenaJ[slot + rank] = jc;
-                    kargs()->out.arenaV[slot + rank] = S.mt[c];
-                }
+                for (int s = 0; s < NJ; ++s) key[s] = (s * G + gl < qq) ? S.Jlist[s * G + gl] : INT_MIN;
+                ranks_in<NJ>(S.Jlist, qq, key, rank);
+#pragma unroll
+                for (int s = 0; s < NJ; ++s)
+                    if (s * G + gl < qq) {
+                        kargs()->out.arenaJ[slot + rank[s]] = key[s];
+                        kargs()->out.arenaV[slot + rank[s]] = S.mt[s * G + gl];
+                    }
             }
             if (gl == 0) {
                 kargs()->out.off[ucol] = slot;

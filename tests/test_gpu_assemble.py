@@ -1,4 +1,4 @@
-"""Assembly of M at the edges of its tiles (256 columns per tile up to 16384 columns, 1024
+"""Assembly of M at the edges of its tiles (256 columns per tile up to 131072 columns, 1024
 beyond; 64 predecessor tiles read at a time): colptr, pattern and values against the
 oracle."""
 import numpy as np
@@ -11,7 +11,7 @@ from tests.parity import compare, run_gpu
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 511, 513, 256 * 64, 256 * 64 + 1, 1024 * 65, 1024 * 66 + 1])
+@pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 511, 513, 256 * 64, 256 * 64 + 1, 256 * 512, 256 * 512 + 1])
 def test_assembly_tile_edges(n):
     """Random columns of 1 to 4 entries with a dominant diagonal: |J_k| varies along the
     columns and across the tile edges."""
