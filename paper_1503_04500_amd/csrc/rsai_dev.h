@@ -437,6 +437,54 @@ __device__ __forceinline__ bool hinsert(int *hk, int key, int &slot) {
     return false;
 }
 
+// Insert up to N keys per lane (key[s] < 0: none): the first probes of all of them in
+// flight together and without lane masks (an absent key probes the element past the
+// table, which holds HEMPTY), then one loop for what collided. h[s] receives the slot,
+// fresh[s] whether the key was not present (also among the keys of this call). Probing is
+// the same as hinsert's; the caller bounds the load so that a free slot is always found.
+template <int LOGHS, int N>
+__device__ __forceinline__ void hinsert_many(int *hk, const int (&key)[N], unsigned (&h)[N], bool (&fresh)[N]) {
+    constexpr unsigned MASK = (1u << LOGHS) - 1u;
+    int old[N];
+#pragma unroll
+    for (int s = 0; s < N; ++s) h[s] = key[s] >= 0 ? hslot<LOGHS>(key[s]) : MASK + 1u;
+#pragma unroll
+    for (int s = 0; s < N; ++s) old[s] = atomicCAS(&hk[h[s]], HEMPTY, key[s]);
+    unsigned open = 0u;  // bit s: key s has found neither itself nor a free slot
+#pragma unroll
+    for (int s = 0; s < N; ++s) open |= (old[s] != HEMPTY && old[s] != key[s]) ? 1u << s : 0u;
+#pragma unroll 1
+    for (int probe = 1; probe < (1 << LOGHS) && wave_any(open != 0u); ++probe) {
+#pragma unroll
+        for (int s = 0; s < N; ++s)
+            if (open & (1u << s)) {
+                h[s] = (h[s] + 1u) & MASK;
+                old[s] = atomicCAS(&hk[h[s]], HEMPTY, key[s]);
+            }
+        open = 0u;
+#pragma unroll
+        for (int s = 0; s < N; ++s) open |= (old[s] != HEMPTY && old[s] != key[s]) ? 1u << s : 0u;
+    }
+#pragma unroll
+    for (int s = 0; s < N; ++s) fresh[s] = key[s] >= 0 && old[s] == HEMPTY;
+}
+// Place of each lane's new item behind the group's first `count` ones, in lane order;
+// advances count (the same in every lane of the group).
+template <int G>
+__device__ __forceinline__ int group_place(bool fresh, int lane, int gl, int &count) {
+    const unsigned long long bal = __ballot(fresh);
+    int ps = count;
+    if constexpr (G == 64) {
+        ps += __popcll(bal & ((1ull << gl) - 1ull));
+        count += __popcll(bal);
+    } else {
+        const unsigned gm = (unsigned)(bal >> (lane / G * G)) & (unsigned)((1ull << G) - 1ull);
+        ps += __popc(gm & ((1u << gl) - 1u));
+        count += __popc(gm);
+    }
+    return ps;
+}
+
 // Slot of key, or -1.
 template <int LOGHS>
 __device__ __forceinline__ int hfind(const int *hk, int key) {

@@ -10,6 +10,17 @@
 // (Algorithm 1, step 7): stored reflectors are applied to the new columns only,
 // then new reflectors are formed.
 //
+// What bounds it is the serial chain of one column's phases at two waves (small tier) or one
+// wave per SIMD: index phases of dependent LDS and memory round trips, and reductions. So the
+// index phases run without lane masks (absent entries go to slots past the arrays' ends),
+// several columns' loads and insertions in flight together, new keys placed by ballots, and
+// the local rows of the columns' first G entries kept as bytes, which the gathers and the
+// residual read instead of probing the row hash. Measured against entry-by-entry insertion
+// with look-ups: 512 x 512 grid, c = 3, eps = 0.4, 0.611 -> 0.585 ms in the small tier;
+// 301 x 301, eps = 0.2, 3.84 -> 3.52 ms in the two group tiers; 64^3 grid 1.66 -> 1.65 ms
+// (columns that outgrow the small tier pay 0.06 ms there and give 0.06 ms back after it);
+// 400 000 power-law columns 19.6 -> 18.9 ms for the whole build.
+//
 // Every loop of Algorithm 1 runs in one pass of the wave's loop; groups that finish
 // take the next column, so different groups of a wave may be at different loops.
 // A column that outgrows the tier's caps is written to a spill record and resumed
@@ -42,11 +53,16 @@ struct TierCfg {
     static constexpr int NEWC = MMAX > QMAX ? MMAX : QMAX;
     static constexpr int RIN = HSI - MMAX - 1;  // candidates inserted per round (I)
     static constexpr int RJN = HSJ - QMAX - 1;  // (J)
-    static constexpr int PREF = (QMAX > CMAX ? QMAX : CMAX) + 1;
     static constexpr int REC = RHDR + QMAX + MMAX + (MMAX + 1) + CMAX;  // spill record ints
-    // small tiers keep a row of every column in registers for the residual of step 4
-    // (all loads in flight together); larger tiers would spill those registers
-    static constexpr bool FASTSEL = QMAX <= 12;
+    // keep the local rows of each column's first G entries (bytes in LDS): the column's wave
+    // waits on its own chain of loads and look-ups, not on LDS space, so the gathers and the
+    // residual read a byte instead of probing the row hash. The wave-wide tier's columns have
+    // few entries per lane and its LDS decides the waves per CU; it looks the rows up.
+    static constexpr bool CROW = G <= 16;
+    // columns whose first G entries are inserted together (the row hash holds them all)
+    static constexpr int CBN = (RIN / G < 1) ? 1 : (RIN / G > 6 ? 6 : RIN / G);
+    // columns whose entries are loaded together for the residual of step 4
+    static constexpr int SELB = QMAX <= 12 ? 6 : 4;
     static_assert(RPL <= 32 && QMAX <= 32, "bit masks");
     static_assert(RIN >= 1 && RJN >= 1, "hash sizes");
     static_assert(QMAX <= MMAX, "row j of the block must exist for every column j");
@@ -90,33 +106,39 @@ struct TierArgs {
 // residual accumulator and column order of the dominant-row phase.
 template <class C>
 struct alignas(16) GLds {
-    double stage[C::STAGE * C::MMAX];
+    // (arrays that the index phases read and write without a lane mask have room past their
+    // end: lanes with nothing to do read what is there and write to the last element)
+    static constexpr int TILE = C::STAGE * C::MMAX;
+    static constexpr int CP = C::QMAX + (C::STAGE > 6 ? C::STAGE : 6);
+    double stage[TILE + 2];
     double mt[C::QMAX];       // solution of the last LS solve, by column slot
-    int64_t cb[C::QMAX];      // first entry of the column in each slot of J (CSC of A)
-    int cl[C::QMAX];          // its length
-    int Ilist[C::MMAX];
+    int cb[CP + 1];           // first entry of the column in each slot of J (CSC of A; nnz < 2^31)
+    int cl[CP + 1];           // its length
+    int Ilist[C::MMAX + 1];
     alignas(16) int Jlist[C::QMAX + 4];  // (three entries of INT_MAX after the last column)
-    int hI[C::HSI];
-    int hJ[C::HSJ];
+    int hI[C::HSI + 1];
+    int hJ[C::HSJ + 1];
     int Rh[CMAX];             // pending dominant rows
     int cnt;
     int fo_lo, fo_hi;         // factor record of a finished column (kept R)
     int pad;
-    unsigned char hIv[C::HSI];  // local row of each key in hI
+    unsigned char hIv[C::HSI + 1];  // local row of each key in hI
+    // local rows of the first G entries of each column of J (entry gl of a column belongs to
+    // lane gl), so that the gathers and the residual look no row up (groups of up to 16
+    // lanes; the wave-wide tier looks them up)
+    unsigned char crow[C::CROW ? (CP + 1) * C::G : 1];
 
     // augmentation phases (K, C, D)
     static constexpr int NEWP = (C::NEWC + 4 + 3) / 4 * 4;  // keys with room for the padding
     __device__ int *newk() { return reinterpret_cast<int *>(stage); }
     __device__ int *news() { return newk() + NEWP; }
-    __device__ int64_t *segb() { return reinterpret_cast<int64_t *>(stage + NEWP); }
-    __device__ int *pref() { return reinterpret_cast<int *>(segb() + C::QMAX); }
     // dominant-row phase (J)
-    __device__ double *racc() { return stage; }
-    __device__ int *ord() { return reinterpret_cast<int *>(stage + C::MMAX); }
+    __device__ double *racc() { return stage; }  // MMAX rows and one for lanes without an entry
+    __device__ int *ord() { return reinterpret_cast<int *>(stage + C::MMAX + 1); }
 
-    static_assert(NEWP * 8 + C::QMAX * 8 + C::PREF * 4 <= C::STAGE * C::MMAX * 8, "scratch fits the tile");
-    static_assert(C::MMAX * 8 + C::QMAX * 4 <= C::STAGE * C::MMAX * 8, "scratch fits the tile");
-    static_assert(C::MMAX < 256, "local rows fit a byte");
+    static_assert(NEWP * 8 <= C::STAGE * C::MMAX * 8, "scratch fits the tile");
+    static_assert((C::MMAX + 1) * 8 + C::QMAX * 4 <= C::STAGE * C::MMAX * 8, "scratch fits the tile");
+    static_assert(C::MMAX < 256 && C::HSI <= 256, "local rows and row-hash slots fit a byte");
 };
 
 

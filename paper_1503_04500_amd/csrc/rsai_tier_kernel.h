@@ -4,6 +4,7 @@
 // compiled with the unrolling it needs).
 #pragma once
 #include <climits>
+#include <type_traits>
 
 #include "rsai_kernels.h"
 #include "rsai_tier.h"
@@ -59,6 +60,8 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
     int64_t u_next = qlo_range + (int64_t)widx * GPW + grp;
 
     // ---- per-group state (uniform inside a group)
+    S.hI[C::HSI] = HEMPTY;  // (what an absent key probes)
+    S.hJ[C::HSJ] = HEMPTY;
     bool busy = false, fin = false;
     int64_t pos = 0;          // position in this launch's queue
     int64_t ucol = 0;         // global column id
@@ -73,8 +76,8 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
     bool park = false;        // plain schedule: write the state out after this loop
     int status = ST_OK;
     double rn = 0.0, fl = 0.0;
-    MatDev A{};
-    if constexpr (!MULTI) A = args.mats[0];
+    // (a group without a column still loads: element 0 of the first matrix's arrays)
+    MatDev A = args.mats[0];
     // ---- per-lane block rows
     double b[RPL][QMAX];
     double y[RPL];
@@ -171,9 +174,9 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
                 for (int t = gl; t < rq; t += G) {
                     int col = RJ[t];
                     S.Jlist[t] = col;
-                    const int64_t b0 = A.colptr[col];
+                    const int b0 = (int)A.colptr[col];
                     S.cb[t] = b0;
-                    S.cl[t] = (int)(A.colptr[col + 1] - b0);
+                    S.cl[t] = (int)A.colptr[col + 1] - b0;
                     int sl;
                     hinsert<C::LOGHSJ>(S.hJ, col, sl);
                 }
@@ -206,6 +209,25 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
             solve = true;
             dropok = false;
         }
+        if constexpr (C::CROW) {
+            // local rows of the stored columns' entries
+            constexpr int RB = 4;
+            for (int t0 = 0; wave_any(resumed && t0 < q); t0 += RB) {
+                int rw[RB];
+#pragma unroll
+                for (int u = 0; u < RB; ++u) {
+                    rw[u] = -1;
+                    if (resumed && t0 + u < q && gl < S.cl[t0 + u]) rw[u] = A.rowidx[S.cb[t0 + u] + gl];
+                }
+#pragma unroll
+                for (int u = 0; u < RB; ++u)
+                    if (rw[u] >= 0) {
+                        const int sl = hfind<C::LOGHSI>(S.hI, rw[u]);
+                        if (sl >= 0) S.crow[(t0 + u) * G + gl] = S.hIv[sl];
+                        else atomicOr(kargs()->err, 16);
+                    }
+            }
+        }
 
         // ====================================== K. J-hat from pending dominant rows
         // (Algorithm 1, step 5: columns of A(R-hat, :) not in J)
@@ -217,59 +239,54 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
             const bool doK = busy && nRh > 0 && !spill;
             // start and prefix length of each pending row's pattern, held in registers
             // by every lane of the group (the loads are independent)
-            int64_t sb[CMAX];
-            int sp[CMAX + 1];
+            int sb[CMAX], sp[CMAX + 1];
             sp[0] = 0;
 #pragma unroll
             for (int t = 0; t < CMAX; ++t) {
-                int64_t b0 = 0, e0 = 0;
-                if (doK && t < nRh) {
-                    const int rt = S.Rh[t];
-                    b0 = A.rowptr[rt];
-                    e0 = A.rowptr[rt + 1];
-                }
+                sb[t] = 0;
+                sp[t + 1] = sp[t];
+                if (t >= P.c) continue;  // (no column has more pending rows)
+                const bool in = doK && t < nRh;
+                const int rt = in ? S.Rh[t] : 0;
+                const int b0 = (int)A.rowptr[rt], e0 = (int)A.rowptr[rt + 1];
                 sb[t] = b0;
-                sp[t + 1] = sp[t] + (int)(e0 - b0);
+                sp[t + 1] = sp[t] + (in ? e0 - b0 : 0);
             }
             const int total = doK ? sp[CMAX] : 0;
             est_m = m;
-            if (doK && gl == 0) S.cnt = 0;
-            wave_sync();
+            int kcnt = 0;  // new columns found
             bool ovf = false;
             for (int base = 0; wave_any(doK && !ovf && base < total); base += C::RJN) {
                 int cand[NRJ];
 #pragma unroll
                 for (int s = 0; s < NRJ; ++s) {
                     const int uu = base + s * G + gl;
-                    cand[s] = -1;
-                    if (doK && !ovf && uu < total && uu < base + C::RJN) {
-                        int64_t b0 = sb[0];
-                        int o0 = 0;
+                    const bool in = doK && !ovf && uu < total && uu < base + C::RJN;
+                    int at = sb[0] + uu;
 #pragma unroll
-                        for (int t = 1; t < CMAX; ++t)
-                            if (uu >= sp[t]) { b0 = sb[t]; o0 = sp[t]; }
-                        cand[s] = A.colidx[b0 + (uu - o0)];
+                    for (int t = 1; t < CMAX; ++t) {
+                        if (t >= P.c) continue;
+                        at = uu >= sp[t] ? sb[t] - sp[t] + uu : at;
                     }
+                    const int col = A.colidx[in ? at : 0];
+                    cand[s] = in ? col : -1;
                 }
+                unsigned h[NRJ];
+                bool isnew[NRJ];
+                hinsert_many<C::LOGHSJ, NRJ>(S.hJ, cand, h, isnew);
 #pragma unroll
                 for (int s = 0; s < NRJ; ++s) {
-                    if (cand[s] >= 0) {
-                        int sl;
-                        if (hinsert<C::LOGHSJ>(S.hJ, cand[s], sl)) {
-                            int ps = atomicAdd(&S.cnt, 1);
-                            if (ps < C::NEWC) S.newk()[ps] = cand[s];
-                        }
-                    }
+                    const int ps = group_place<G>(isnew[s], lane, gl, kcnt);
+                    S.newk()[(isnew[s] && ps < C::NEWC) ? ps : GLds<C>::NEWP - 1] = cand[s];
                 }
-                wave_sync();
-                if (doK && !ovf && q + S.cnt > QMAX) {
+                if (doK && !ovf && q + kcnt > QMAX) {
                     // |J-hat| extrapolated from the share of new columns seen so far
                     ovf = true;
-                    est_q = q + (int)ceilf((float)S.cnt * (float)total / (float)min(base + C::RJN, total));
+                    est_q = q + (int)ceilf((float)kcnt * (float)total / (float)min(base + C::RJN, total));
                 }
                 wave_sync();
             }
-            const int nnew = (doK && !ovf) ? S.cnt : 0;
+            const int nnew = (doK && !ovf) ? kcnt : 0;
             if (nnew > 0 && gl < 4) S.newk()[nnew + gl] = INT_MAX;
             wave_sync();
             if (doK) {
@@ -318,63 +335,122 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
         // ================================ C. I-hat: rows of the new columns not in I
         {
             const bool doC = busy && !spill && p > 0;
-            // pending columns in parallel: start -> LDS, length -> LDS, then every lane
-            // forms the prefix in registers
-            if (doC) {
-                for (int t = gl; t < p; t += G) {
-                    const int j = S.Jlist[q + t];
-                    const int64_t b0 = A.colptr[j];
-                    const int len = (int)(A.colptr[j + 1] - b0);
-                    S.segb()[t] = b0;
-                    S.pref()[t] = len;
-                    S.cb[q + t] = b0;  // kept by slot for the gathers and the residual
-                    S.cl[q + t] = len;
-                }
-                if (gl == 0) S.cnt = 0;
+            // pending columns the wave has at most: the unrolled batches stop there
+            const int pmaxw = wave_max_i(doC ? p : 0);
+            // pending columns in parallel: start and length -> LDS
+            int ctot = 0;
+#pragma unroll
+            for (int s = 0; s < (QMAX + G - 1) / G; ++s) {
+                const int t = s * G + gl;
+                const bool in = doC && t < p;
+                const int j = in ? S.Jlist[q + t] : 0;
+                const int b0 = (int)A.colptr[j], len = (int)A.colptr[j + 1] - b0;
+                S.cb[in ? q + t : GLds<C>::CP] = b0;  // kept by slot for the gathers and the residual
+                S.cl[in ? q + t : GLds<C>::CP] = len;
+                ctot += in ? len : 0;
             }
+            const int total = gsum_i<G>(ctot);
             wave_sync();
-            int cpx[QMAX + 1];
-            cpx[0] = 0;
-#pragma unroll
-            for (int t = 0; t < QMAX; ++t) cpx[t + 1] = cpx[t] + ((doC && t < p) ? S.pref()[t] : 0);
-            const int total = doC ? cpx[QMAX] : 0;
             bool ovf = false;
-            for (int base = 0; wave_any(doC && !ovf && base < total); base += C::RIN) {
-                int cand[NRI];
-#pragma unroll
-                for (int s = 0; s < NRI; ++s) {
-                    const int uu = base + s * G + gl;
-                    cand[s] = -1;
-                    if (doC && !ovf && uu < total && uu < base + C::RIN) {
-                        int seg = 0, o0 = 0;
-#pragma unroll
-                        for (int t = 1; t < QMAX; ++t)
-                            if (uu >= cpx[t]) { seg = t; o0 = cpx[t]; }
-                        cand[s] = A.rowidx[S.segb()[seg] + (uu - o0)];
-                    }
+            int ccnt = 0;   // new rows found
+            int seen = 0;   // entries inserted
+            // new rows of one insertion: appended to the list in lane order
+            auto take = [&](int row, unsigned slot, bool fresh) {
+                const int ps = group_place<G>(fresh, lane, gl, ccnt);
+                // (room for one more entry past the last)
+                const int at = (fresh && ps < C::NEWC) ? ps : GLds<C>::NEWP - 1;
+                S.newk()[at] = row;
+                S.news()[at] = (int)slot;
+            };
+            auto full = [&]() {
+                if (doC && !ovf && m + ccnt > MMAX) {
+                    // |I-hat| extrapolated from the share of new rows seen so far
+                    ovf = true;
+                    est_m = m + (int)ceilf((float)ccnt * (float)total / (float)min(seen, total));
+                    est_q = q + p;
                 }
+            };
+            if constexpr (C::CROW) {
+                // entry gl of CBN columns at a time (the insertions of one lane's entries in
+                // flight together), then the rest of the longer ones
+                bool longer = false;
+                auto batch = [&](auto nb, int t0) {
+                    constexpr int NB = decltype(nb)::value;
+                    int rw[NB];
+                    unsigned h[NB];
+                    bool isnew[NB];
 #pragma unroll
-                for (int s = 0; s < NRI; ++s) {
-                    if (cand[s] >= 0) {
-                        int sl;
-                        if (hinsert<C::LOGHSI>(S.hI, cand[s], sl)) {
-                            int ps = atomicAdd(&S.cnt, 1);
-                            if (ps < C::NEWC) { S.newk()[ps] = cand[s]; S.news()[ps] = sl; }
+                    for (int u = 0; u < NB; ++u) {
+                        // (a slot past the last column: its length counts as 0)
+                        const int c = min(q + t0 + u, GLds<C>::CP);
+                        const int len = (doC && !ovf && t0 + u < p) ? S.cl[c] : 0;
+                        const int row = A.rowidx[gl < len ? S.cb[c] + gl : 0];
+                        rw[u] = gl < len ? row : -1;
+                        longer |= len > G;
+                        seen += min(len, G);
+                    }
+                    hinsert_many<C::LOGHSI, NB>(S.hI, rw, h, isnew);
+#pragma unroll
+                    for (int u = 0; u < NB; ++u) {
+                        S.crow[(rw[u] >= 0 ? q + t0 + u : GLds<C>::CP) * G + gl] = (unsigned char)h[u];
+                        take(rw[u], h[u], isnew[u]);
+                    }
+                    full();
+                };
+                // (a wave whose columns are all at loop 0 has one each: no batch for that)
+                if (pmaxw == 1) batch(std::integral_constant<int, 1>{}, 0);
+                else
+                    for (int t0 = 0; wave_any(doC && !ovf && t0 < p); t0 += C::CBN)
+                        batch(std::integral_constant<int, C::CBN>{}, t0);
+                if (wave_any(longer && !ovf)) {
+                    for (int t = 0; wave_any(longer && !ovf && t < p); ++t) {
+                        const int e1 = (longer && !ovf && t < p) ? S.cl[q + t] : 0;
+                        for (int e = G; wave_any(!ovf && e < e1); e += G) {
+                            int rw[1];
+                            unsigned h[1];
+                            bool isnew[1];
+                            rw[0] = (!ovf && e + gl < e1) ? A.rowidx[S.cb[q + t] + e + gl] : -1;
+                            seen += (!ovf && e < e1) ? min(e1 - e, G) : 0;
+                            hinsert_many<C::LOGHSI, 1>(S.hI, rw, h, isnew);
+                            take(rw[0], h[0], isnew[0]);
+                            full();
                         }
                     }
                 }
-                wave_sync();
-                if (doC && !ovf && m + S.cnt > MMAX) {
-                    // |I-hat| extrapolated from the share of new rows seen so far
-                    ovf = true;
-                    est_m = m + (int)ceilf((float)S.cnt * (float)total / (float)min(base + C::RIN, total));
-                    est_q = q + p;
+            } else {
+                // a wave per column of the build: the entries of all pending columns side by
+                // side, found by their prefix
+                int cpx[QMAX + 1];
+                cpx[0] = 0;
+#pragma unroll
+                for (int t = 0; t < QMAX; ++t) cpx[t + 1] = cpx[t] + ((doC && t < p) ? S.cl[q + t] : 0);
+                for (int base = 0; wave_any(doC && !ovf && base < total); base += C::RIN) {
+                    int rw[NRI];
+                    unsigned h[NRI];
+                    bool isnew[NRI];
+#pragma unroll
+                    for (int s = 0; s < NRI; ++s) {
+                        const int uu = base + s * G + gl;
+                        rw[s] = -1;
+                        if (doC && !ovf && uu < total && uu < base + C::RIN) {
+                            int seg = 0, o0 = 0;
+#pragma unroll
+                            for (int t = 1; t < QMAX; ++t)
+                                if (uu >= cpx[t]) { seg = t; o0 = cpx[t]; }
+                            rw[s] = A.rowidx[S.cb[q + seg] + (uu - o0)];
+                        }
+                    }
+                    seen = base + C::RIN;
+                    hinsert_many<C::LOGHSI, NRI>(S.hI, rw, h, isnew);
+#pragma unroll
+                    for (int s = 0; s < NRI; ++s) take(rw[s], h[s], isnew[s]);
+                    full();
                 }
-                wave_sync();
             }
+            wave_sync();
             if (doC && ovf) spill = true;
             // ============================ D. number the new rows (ascending order)
-            const int nnew = (doC && !ovf) ? S.cnt : 0;
+            const int nnew = (doC && !ovf) ? ccnt : 0;
             int kpos = -1;
             if (nnew > 0 && gl < 4) S.newk()[nnew + gl] = INT_MAX;
             wave_sync();
@@ -385,16 +461,37 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
                 ranks_in<NNEW>(S.newk(), nnew, key, rank);
 #pragma unroll
                 for (int s = 0; s < NNEW; ++s) {
-                    if (s * G + gl < nnew) {
-                        const int li = m + rank[s];
-                        S.Ilist[li] = key[s];
-                        S.hIv[S.news()[s * G + gl]] = li;
-                        if (key[s] == k) kpos = li;
-                    }
+                    const bool in = s * G + gl < nnew;
+                    const int li = in ? m + rank[s] : MMAX;
+                    const int sl = S.news()[s * G + gl];
+                    S.Ilist[li] = key[s];
+                    S.hIv[in ? sl : C::HSI] = (unsigned char)li;
+                    kpos = (in && key[s] == k) ? li : kpos;
                 }
             }
             kpos = gmax_i<G>(kpos);
             wave_sync();
+            if constexpr (C::CROW) {
+                // hash slots of the new columns' entries -> their local rows
+                auto batch = [&](auto nb, int t0) {
+                    constexpr int NB = decltype(nb)::value;
+                    int sl[NB], at[NB];
+#pragma unroll
+                    for (int u = 0; u < NB; ++u) {
+                        at[u] = ((doC && !ovf && t0 + u < p) ? q + t0 + u : GLds<C>::CP) * G + gl;
+                        // (a lane without an entry there reads any slot of the table)
+                        sl[u] = S.crow[at[u]] & (C::HSI - 1);
+                    }
+#pragma unroll
+                    for (int u = 0; u < NB; ++u) sl[u] = S.hIv[sl[u]];
+#pragma unroll
+                    for (int u = 0; u < NB; ++u) S.crow[at[u]] = (unsigned char)sl[u];
+                };
+                if (pmaxw == 1) batch(std::integral_constant<int, 1>{}, 0);
+                else
+                    for (int t0 = 0; wave_any(doC && !ovf && t0 < p); t0 += C::CBN)
+                        batch(std::integral_constant<int, C::CBN>{}, t0);
+            }
             if (doC && !ovf) {
                 if (kpos >= 0) {
                     kidx = kpos;
@@ -499,63 +596,76 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
             for (int it = 0; wave_any(act && qlo + it * STAGE < qn); ++it) {
                 const int c0 = qlo + it * STAGE;
                 const bool ract = act && c0 < qn;
+                const int nstage = wave_max_i(ract ? qn - c0 : 0);  // columns staged at most
+                // first G entries of each staged column: all loads issued together, a lane
+                // without an entry loads the first one and writes past the tile
+                bool more = false;
+                auto put = [&](auto nb) {
+                    constexpr int NB = decltype(nb)::value;
 #pragma unroll
-                for (int s = 0; s < STAGE; ++s)
+                    for (int s = 0; s < NB; ++s)
 #pragma unroll
-                    for (int r = 0; r < RPL; ++r) S.stage[s * MMAX + r * G + gl] = 0.0;
-                wave_sync();
-                // first G entries of each staged column: all loads issued together
-                int64_t ce1[STAGE], ce0[STAGE];
-                int rw[STAGE];
-                double vv[STAGE];
+                        for (int r = 0; r < RPL; ++r) S.stage[s * MMAX + r * G + gl] = 0.0;
+                    wave_sync();
+                    int ce0[NB], cln[NB], li[NB];
+                    double vv[NB];
 #pragma unroll
-                for (int s = 0; s < STAGE; ++s) {
-                    const int c = c0 + s;
-                    ce0[s] = 0;
-                    ce1[s] = 0;
-                    if (ract && c < qn) {
+                    for (int s = 0; s < NB; ++s) {
+                        const int c = min(c0 + s, GLds<C>::CP);
                         ce0[s] = S.cb[c];
-                        ce1[s] = ce0[s] + S.cl[c];
+                        cln[s] = (ract && c < qn) ? S.cl[c] : 0;
+                        if constexpr (C::CROW) li[s] = S.crow[c * G + gl];
                     }
-                }
 #pragma unroll
-                for (int s = 0; s < STAGE; ++s) {
-                    const int64_t e = ce0[s] + gl;
-                    rw[s] = -1;
-                    vv[s] = 0.0;
-                    if (e < ce1[s]) {
-                        rw[s] = A.rowidx[e];
+                    for (int s = 0; s < NB; ++s) {
+                        more |= cln[s] > G;
+                        const int e = gl < cln[s] ? ce0[s] + gl : 0;
                         vv[s] = A.val[e];
+                        if constexpr (!C::CROW) li[s] = A.rowidx[e];
                     }
-                }
 #pragma unroll
-                for (int s = 0; s < STAGE; ++s) {
-                    if (rw[s] >= 0) {
-                        const int sl = hfind<C::LOGHSI>(S.hI, rw[s]);
-                        const int li = sl >= 0 ? S.hIv[sl] : -1;
-                        if (li >= 0 && li < MMAX) S.stage[s * MMAX + li] = vv[s];
-                        else lookup_fail = true;
+                    for (int s = 0; s < NB; ++s) {
+                        if constexpr (C::CROW) {
+                            S.stage[gl < cln[s] ? s * MMAX + li[s] : GLds<C>::TILE] = vv[s];
+                        } else if (gl < cln[s]) {
+                            const int sl = hfind<C::LOGHSI>(S.hI, li[s]);
+                            const int l2 = sl >= 0 ? S.hIv[sl] : MMAX;
+                            if (l2 < MMAX) S.stage[s * MMAX + l2] = vv[s];
+                            else lookup_fail = true;
+                        }
                     }
-                    // entries beyond the first G (long columns)
-                    for (int64_t e = ce0[s] + G + gl; e < ce1[s]; e += G) {
-                        const int sl = hfind<C::LOGHSI>(S.hI, A.rowidx[e]);
-                        const int li = sl >= 0 ? S.hIv[sl] : -1;
-                        if (li >= 0 && li < MMAX) S.stage[s * MMAX + li] = A.val[e];
-                        else lookup_fail = true;
+                };
+                if (nstage == 1) put(std::integral_constant<int, 1>{});
+                else put(std::integral_constant<int, STAGE>{});
+                // entries beyond the first G (long columns)
+                if (wave_any(more)) {
+#pragma unroll 1
+                    for (int s = 0; s < STAGE; ++s) {
+                        const int c = c0 + s;
+                        const bool in = ract && c < qn;
+                        const int b0 = in ? S.cb[c] : 0, e1 = in ? b0 + S.cl[c] : 0;
+                        for (int e = b0 + G + gl; e < e1; e += G) {
+                            const int sl = hfind<C::LOGHSI>(S.hI, A.rowidx[e]);
+                            const int l2 = sl >= 0 ? S.hIv[sl] : -1;
+                            if (l2 >= 0 && l2 < MMAX) S.stage[s * MMAX + l2] = A.val[e];
+                            else lookup_fail = true;
+                        }
                     }
                 }
                 wave_sync();
-                if (ract) {
+                // (columns outside the wave's staged ranges are passed over; a group whose
+                // range does not hold column c keeps what it has)
+                const int cfirst = -wave_max_i(ract ? -c0 : -QMAX), clast = wave_max_i(ract ? c0 : -STAGE) + STAGE;
 #pragma unroll
-                    for (int c = 0; c < QMAX; ++c) {
-                        if (c >= qmaxw) continue;
-                        const int s = c - c0;
-                        if (s >= 0 && s < STAGE && c < qn) {
+                for (int c = 0; c < QMAX; ++c) {
+                    if (c < cfirst || c >= clast || c >= qmaxw) continue;
+                    const int s = c - c0;
+                    const bool in = ract && s >= 0 && s < STAGE && c < qn;
+                    const int at = (in ? s * MMAX : 0) + gl;
 #pragma unroll
-                            for (int r = 0; r < RPL; ++r) {
-                                b[r][c] = S.stage[s * MMAX + r * G + gl];
-                            }
-                        }
+                    for (int r = 0; r < RPL; ++r) {
+                        const double x = S.stage[at + r * G];
+                        b[r][c] = in ? x : b[r][c];
                     }
                 }
                 wave_sync();
@@ -709,8 +819,7 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
                     if (__popc(keep) == q) dact = false;
                 }
                 if (wave_any(dact)) {
-                    int jv[(QMAX + G - 1) / G], lv[(QMAX + G - 1) / G];
-                    int64_t bv0[(QMAX + G - 1) / G];
+                    int jv[(QMAX + G - 1) / G], lv[(QMAX + G - 1) / G], bv0[(QMAX + G - 1) / G];
                     if (dact) {
                         if (keep == 0u) {
                             // keep the largest |m_j| (smaller column index on ties)
@@ -744,6 +853,21 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
                                 S.Jlist[d] = jv[s];
                                 S.cb[d] = bv0[s];
                                 S.cl[d] = lv[s];
+                            }
+                        }
+                        if constexpr (C::CROW) {
+                            // (a lane's own bytes; a column only moves towards the front)
+                            constexpr int RB = 6;
+                            static_assert(QMAX % RB == 0, "batches of columns");
+#pragma unroll
+                            for (int c0 = 0; c0 < QMAX; c0 += RB) {
+                                int rv[RB];
+#pragma unroll
+                                for (int u = 0; u < RB; ++u) rv[u] = S.crow[(c0 + u) * G + gl];
+#pragma unroll
+                                for (int u = 0; u < RB; ++u)
+                                    if (c0 + u < q && (keep & (1u << (c0 + u))))
+                                        S.crow[__popc(keep & ((1u << (c0 + u)) - 1u)) * G + gl] = (unsigned char)rv[u];
                             }
                         }
                         for (int t = gl; t < C::HSJ; t += G) S.hJ[t] = HEMPTY;
@@ -795,57 +919,56 @@ __global__ __launch_bounds__(64, C::WPS) void tier_kernel(TierArgs args) {
             }
             wave_sync();
             bool lookup_fail2 = false;
-            // Fast path: when no column of the group has more than G entries, each lane
-            // holds at most one entry per column, and the loads of all columns go out
-            // together; the accumulation below keeps the ascending column order.
-            bool shortcols = false;
-            if constexpr (C::FASTSEL) {
-                shortcols = true;
-                int rw2[QMAX];
-                double vv2[QMAX];
+            // SELB columns at a time, their first G entries' loads in flight together; the
+            // accumulation keeps the ascending column order (rows of one column are
+            // distinct; successive columns are ordered by the wave's in-order LDS execution)
+            auto batch = [&](auto nb, int t0) {
+                constexpr int NB = decltype(nb)::value;
+                int cc[NB], lr[NB], cl[NB];
+                double vv[NB], mc[NB];
+                bool more = false;
 #pragma unroll
-                for (int t = 0; t < QMAX; ++t) {
-                    rw2[t] = -1;
-                    vv2[t] = 0.0;
-                    if (sel && t < q) {
-                        const int64_t e0 = S.cb[ord[t]], e1 = e0 + S.cl[ord[t]];
-                        if (e1 - e0 > G) shortcols = false;
-                        const int64_t e = e0 + gl;
-                        if (e < e1) {
-                            rw2[t] = A.rowidx[e];
-                            vv2[t] = A.val[e];
-                        }
-                    }
+                for (int u = 0; u < NB; ++u) cc[u] = (sel && t0 + u < q) ? ord[min(t0 + u, QMAX - 1)] : -1;
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {
+                    const int c = cc[u] >= 0 ? cc[u] : 0;
+                    cl[u] = cc[u] >= 0 ? S.cl[c] : 0;
+                    mc[u] = mts[c];
+                    more |= cl[u] > G;
+                    const int e = gl < cl[u] ? S.cb[c] + gl : 0;
+                    int r0;
+                    if constexpr (C::CROW) r0 = S.crow[c * G + gl];
+                    else r0 = A.rowidx[e];
+                    lr[u] = gl < cl[u] ? r0 : -1;
+                    vv[u] = A.val[e];
                 }
-                shortcols = gsum_i<G>(shortcols ? 0 : 1) == 0;
-                if (sel && shortcols) {
+                const bool wmore = wave_any(more);
 #pragma unroll
-                    for (int t = 0; t < QMAX; ++t) {
-                        if (rw2[t] >= 0) {
-                            const double mc = mts[ord[t]];
-                            const int sl = hfind<C::LOGHSI>(S.hI, rw2[t]);
-                            const int li = sl >= 0 ? S.hIv[sl] : -1;
-                            if (li >= 0 && li < MMAX) racc[li] = __fma_rn(vv2[t], mc, racc[li]);
+                for (int u = 0; u < NB; ++u) {
+                    if constexpr (C::CROW) {
+                        // (a lane without an entry accumulates past the rows)
+                        const int l2 = lr[u] >= 0 ? lr[u] : MMAX;
+                        racc[l2] = __fma_rn(vv[u], mc[u], racc[l2]);
+                    } else if (lr[u] >= 0) {
+                        const int sl = hfind<C::LOGHSI>(S.hI, lr[u]);
+                        const int l2 = sl >= 0 ? S.hIv[sl] : MMAX;
+                        if (l2 < MMAX) racc[l2] = __fma_rn(vv[u], mc[u], racc[l2]);
+                        else lookup_fail2 = true;
+                    }
+                    if (wmore && cl[u] > G) {
+                        const int e1 = S.cb[cc[u]] + cl[u];
+                        for (int e = S.cb[cc[u]] + G + gl; e < e1; e += G) {
+                            const int sl = hfind<C::LOGHSI>(S.hI, A.rowidx[e]);
+                            const int l2 = sl >= 0 ? S.hIv[sl] : -1;
+                            if (l2 >= 0 && l2 < MMAX) racc[l2] = __fma_rn(A.val[e], mc[u], racc[l2]);
                             else lookup_fail2 = true;
                         }
                     }
                 }
-            }
-            for (int t = 0; t < qmaxw; ++t) {
-                if (sel && !shortcols && t < q) {
-                    const int c = ord[t];
-                    const double mc = mts[c];
-                    const int64_t e1 = S.cb[c] + S.cl[c];
-                    for (int64_t e = S.cb[c] + gl; e < e1; e += G) {
-                        const int sl = hfind<C::LOGHSI>(S.hI, A.rowidx[e]);
-                        const int li = sl >= 0 ? S.hIv[sl] : -1;
-                        if (li >= 0 && li < MMAX) racc[li] = __fma_rn(A.val[e], mc, racc[li]);
-                        else lookup_fail2 = true;
-                    }
-                }
-                // rows of one column are distinct; successive columns are ordered by
-                // the wave's in-order LDS execution
-            }
+            };
+            if (qmaxw == 1) batch(std::integral_constant<int, 1>{}, 0);
+            else
+                for (int t0 = 0; t0 < qmaxw; t0 += C::SELB) batch(std::integral_constant<int, C::SELB>{}, t0);
             wave_sync();
             if (lookup_fail2) atomicOr(kargs()->err, 16);
             double ra[RPL];
