@@ -50,7 +50,8 @@ struct ColOut {              // per global column
 
 // Reserve a factor record of q columns; -1 when the arena is full (the adjoint then
 // refactorises that column).
-__device__ __forceinline__ long long fac_reserve(const ColOut &o, int q) {
+template <class O>  // ColOut, in any address space
+__device__ __forceinline__ long long fac_reserve(const O &o, int q) {
     const unsigned long long need = (unsigned long long)(q + q * (q + 1) / 2);
     const unsigned long long at = atomicAdd(o.fac_cur, need);
     return (at + need <= (unsigned long long)o.fac_cap) ? (long long)at : -1LL;

@@ -1,4 +1,4 @@
-// Sparse-block size class of the RSAI(tol) build: one 256-thread workgroup per
+// Sparse-block size class of the RSAI(tol) build: one workgroup (128 or 256 threads) per
 // column, for LS blocks A(I_k, J_k) that outgrow the register tiers but are mostly
 // structurally empty (long sparse columns with few rows in common, as in matrices
 // with power-law column lengths). Up to 8192 rows and WIDE_QMAX columns.
@@ -17,8 +17,20 @@
 // columns of J_k that hold the row and a flag for rows already used as dominant
 // rows; the residual for step 4 is formed from the sparse columns with the columns
 // taken in ascending global order, so exact ties reach the smaller-index rule.
+//
+// What bounds it is the latency of a column's dependent phases at the few columns that a CU's
+// LDS holds (four in level 0): a mean column has 600 entries, 17 columns of J and 3 shared
+// rows, so neither bandwidth nor arithmetic is near its limit. Hence the entries of J's
+// columns lie side by side over all lanes (not a wave per column), loaded once, and their
+// rows' hash slots stay in registers for the sums, the drop and the residual; steps that a
+// wave can do alone take no workgroup barrier; and the compressed solve eliminates the columns
+// of one shared row in closed form. 400 000 power-law columns (2 to 200 entries), c = 3,
+// eps = 0.4: a wave per column, every entry looked up again per phase and all columns stepped
+// through, 16.0 ms in levels 0 to 3; entries in registers 12.6 ms; closed form 9.9 ms.
+//
 // Columns arrive as spill records of the previous class. A column whose |I_k| or
 // compressed block outgrows this class moves on to the next one.
+#include <cfloat>
 #include <climits>
 #include <type_traits>
 
@@ -27,8 +39,6 @@
 namespace rsai {
 
 namespace {
-constexpr int NT = 256;                 // threads per column
-constexpr int NW = NT / 64;             // waves
 constexpr int QM = WIDE_QMAX;
 constexpr int LOGHJ = 8;                // column hash: 256 slots
 constexpr int HJ = 1 << LOGHJ;
@@ -38,18 +48,22 @@ constexpr int HJ = 1 << LOGHJ;
 //   BLK  doubles of the compressed block, (S + q) x (q + 1), row-major
 //   SHV  doubles of the shared rows' values, S x q
 //   SMAX shared rows
-template <int LOGH, int BLK, int SHV, int SMAX>
+template <int NT, int LOGH, int BLK, int SHV, int SMAX, int KE>
 struct WLds {
+    static constexpr int NW = NT / 64;  // waves
     static constexpr int HS = 1 << LOGH;
-    int hk[HS];             // row keys
+    int hk[HS + 1];         // row keys (one more slot for lanes without a key)
     unsigned hv[HS / 4];    // one byte per slot: bits 0-6 columns of J holding the row, bit 7 row in R
     int hJ[HJ];             // J as a set
-    double blk[BLK];
+    double blk[BLK];        // also the entries' squares while the private sums are formed
     double shv[SHV];
     double s2[64];          // private rows of each column: sum of squares
     double mt[64], rd[64];  // solution by slot, diagonal of R
-    int64_t cb[64];         // first entry of each column of J
+    unsigned long long start[NW * KE];  // bit u: entry u of J's columns is a column's first
+    int cb[64];             // first entry of each column of J (nnz < 2^31)
     int clen[64];
+    int pre[65];            // entries of the columns before it, side by side in slot order
+    int cbo[64];            // cb - pre
     int Jl[64];             // J, slot order
     int ord[64];            // slots in ascending column order
     int srow[SMAX];         // shared rows, ascending
@@ -63,7 +77,7 @@ struct WLds {
     int cvg[NW];
     double akv;             // a_kj when k is a private row of column slot kcol
     int kcol;
-    int cnt, nsh, flag, nsl, slovf, nsh2;
+    int cnt, nsh, flag, nsl, slovf, nsh2, madd;
     double rn;
 };
 
@@ -71,20 +85,37 @@ template <class L>
 __device__ __forceinline__ unsigned hget(const L &S, int sl) {
     return (S.hv[sl >> 2] >> ((sl & 3) * 8)) & 0xFFu;
 }
+template <class L>
+__device__ __forceinline__ void now_shared(L &S, int row) {
+    const int ps = atomicAdd(&S.nsl, 1);
+    if (ps < (int)(sizeof(S.slist) / sizeof(int))) S.slist[ps] = row; else S.slovf = 1;
+}
 // one more column holds the row of slot sl; a row that becomes shared (two holders)
 // joins the candidate list of the next shared-row scan
 template <class L>
 __device__ __forceinline__ void hinc(L &S, int sl, int row) {
     const unsigned old = atomicAdd(&S.hv[sl >> 2], 1u << ((sl & 3) * 8));
-    if (((old >> ((sl & 3) * 8)) & 0x7Fu) == 1u) {
-        const int ps = atomicAdd(&S.nsl, 1);
-        if (ps < (int)(sizeof(S.slist) / sizeof(int))) S.slist[ps] = row; else S.slovf = 1;
-    }
+    if (((old >> ((sl & 3) * 8)) & 0x7Fu) == 1u) now_shared(S, row);
 }
 template <class L>
 __device__ __forceinline__ void hdec(L &S, int sl) { atomicSub(&S.hv[sl >> 2], 1u << ((sl & 3) * 8)); }
 template <class L>
 __device__ __forceinline__ void hsetR(L &S, int sl) { atomicOr(&S.hv[sl >> 2], 0x80u << ((sl & 3) * 8)); }
+
+// The matrix's pointers and the kernel's arguments, read through pointers whose value the
+// compiler cannot see: loaded where a phase uses them instead of being held in scalar
+// registers across the solve.
+using CMat = const __attribute__((address_space(4))) MatDev;
+__device__ __forceinline__ CMat &matrix(CMat *p) {
+    asm volatile("" : "+s"(p));
+    return *p;
+}
+using CArgs = const __attribute__((address_space(4))) WideArgs;
+__device__ __forceinline__ CArgs &kargs() {
+    CArgs *p = (CArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *p;
+}
 
 // wave-wide sum; every lane gets the bitwise-same value
 __device__ __forceinline__ double wsum(double x) {
@@ -108,76 +139,44 @@ __device__ __forceinline__ int sfind(const int *srow, int nsh, int row) {
     }
     return -1;
 }
-// Visit every entry of the columns c0 + wid + NW*s (below c1) of J with the lanes of
-// one wave, one column after another: f(c, row, val) for each entry, then done(c).
-// The first 64 entries of the next HB columns are loaded together ahead of use; the
-// loop over columns stays rolled to keep the code small.
-// Columns for which want(c) is false are skipped without loading their entries.
-template <bool VAL, class L, class F, class D, class W>
-__device__ __forceinline__ void wave_cols_if(const L &S, const MatDev &A, int c0, int c1, int wid, int lane, F &&f,
-                                             D &&done, W &&want) {
-    constexpr int HB = 8;
-    for (int cb0 = c0 + wid; cb0 < c1; cb0 += NW * HB) {
-        int rr[HB];
-        double vv[HB];
+// inclusive prefix sum over the wave
+__device__ __forceinline__ int wscan(int x, int lane) {
 #pragma unroll
-        for (int s = 0; s < HB; ++s) {
-            const int c = cb0 + NW * s;
-            rr[s] = -1;
-            vv[s] = 0.0;
-            if (c < c1 && lane < S.clen[c] && want(c)) {
-                const int64_t e = S.cb[c] + lane;
-                rr[s] = A.rowidx[e];
-                if (VAL) vv[s] = A.val[e];
-            }
-        }
-#pragma unroll 1
-        for (int s = 0; s < HB; ++s) {
-            const int c = cb0 + NW * s;
-            if (c >= c1) break;
-            const int r0 = rr[0];
-            const double v0 = vv[0];
-#pragma unroll
-            for (int t = 0; t < HB - 1; ++t) {
-                rr[t] = rr[t + 1];
-                vv[t] = vv[t + 1];
-            }
-            if (r0 >= 0) f(c, r0, v0);
-            const int len = S.clen[c];
-            if (len > 64 && want(c)) {
-                const int64_t e0 = S.cb[c];
-                for (int t = 64 + lane; t < len; t += 64) f(c, A.rowidx[e0 + t], VAL ? A.val[e0 + t] : 0.0);
-            }
-            done(c);
-        }
+    for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(x, d);
+        x += lane >= d ? y : 0;
     }
-}
-template <bool VAL, class L, class F, class D>
-__device__ __forceinline__ void wave_cols(const L &S, const MatDev &A, int c0, int c1, int wid, int lane, F &&f,
-                                          D &&done) {
-    wave_cols_if<VAL>(S, A, c0, c1, wid, lane, f, done, [](int) { return true; });
+    return x;
 }
 }  // namespace
 
-template <int LOGH, int BLK, int SHV, int SMAX, int WPC>
-__global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
+template <int NT, int LOGH, int BLK, int SHV, int SMAX, int KE, int WPC>
+__global__ __launch_bounds__(NT, WPC * NT / 256) void wide_kernel(WideArgs args) {
     constexpr int HS = 1 << LOGH;
     constexpr int MM = HS / 2;  // row hash load at most one half
-    __shared__ WLds<LOGH, BLK, SHV, SMAX> S;
+    constexpr int KU = KE * NT;  // entries of J's columns held in registers
+    constexpr int SU = 8;        // shared rows of the one-wave QR and drop
+    static_assert(KU <= BLK && KE % 4 == 0 && KE <= 64 && HS <= 1 << 16, "entry registers");
+    constexpr int NW = NT / 64;  // waves
+    static_assert(SMAX <= NT && QM < NT, "a thread per shared row and per column");
+    __shared__ WLds<NT, LOGH, BLK, SHV, SMAX, KE> S;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     if (*args.err & ERR_SKIP) return;
     const BuildParams P = args.P;
+    const bool whole = args.out.fac != nullptr;  // R is kept: every column takes its step of the QR
     const int64_t Q = min((int64_t)(*args.rec_in_count), args.rec_in_cap);
 
     for (int64_t pos = blockIdx.x; pos < Q; pos += gridDim.x) {
         const int32_t *rec = args.rec_in + pos * (int64_t)args.rec_in_stride;
-        const int ucol = rec[0], mat = rec[1], k = rec[2];
-        int l = rec[3], q = rec[4], m = rec[5];
-        const int nR0 = rec[6];
-        int nRh = rec[7];
+        // (the record's header is the same for every lane: scalar registers)
+        auto uni = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+        const int ucol = uni(rec[0]), mat = uni(rec[1]), k = uni(rec[2]);
+        int l = uni(rec[3]), q = uni(rec[4]), m = uni(rec[5]);
+        const int nR0 = uni(rec[6]);
+        int nRh = uni(rec[7]);
         double fl = __longlong_as_double(((long long)rec[9] << 32) | (long long)(unsigned)rec[8]);
-        bool linc = (rec[10] & 1) != 0;
-        const MatDev A = args.mats[mat];
+        bool linc = (uni(rec[10]) & 1) != 0;
+        CMat *const Am = (CMat *)(args.mats + mat);
         const int32_t *RJ = rec + RHDR, *RI = RJ + q, *RR = RI + m, *RHp = RR + nR0;
         int status = ST_OK;
         bool spill = false, pend = false, pend_drop = false;
@@ -190,15 +189,15 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
         for (int t = tid; t < HS; t += NT) S.hk[t] = HEMPTY;
         for (int t = tid; t < HS / 4; t += NT) S.hv[t] = 0u;
         for (int t = tid; t < HJ; t += NT) S.hJ[t] = HEMPTY;
-        if (tid == 0) { S.flag = 0; S.nsl = 0; S.slovf = 0; }
+        if (tid == 0) { S.flag = 0; S.nsl = 0; S.slovf = 0; S.madd = 0; S.hk[HS] = HEMPTY; }
         __syncthreads();
         if (q > QM || m > MM || nRh > CMAX) status = ST_CAP;  // larger than any register tier
         if (status == ST_OK) {
             for (int t = tid; t < q; t += NT) {
                 const int col = RJ[t];
                 S.Jl[t] = col;
-                S.cb[t] = A.colptr[col];
-                S.clen[t] = (int)(A.colptr[col + 1] - S.cb[t]);
+                S.cb[t] = (int)matrix(Am).colptr[col];
+                S.clen[t] = (int)matrix(Am).colptr[col + 1] - S.cb[t];
                 int sl;
                 hinsert<LOGHJ>(S.hJ, col, sl);
             }
@@ -210,14 +209,6 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
         }
         __syncthreads();
         if (status == ST_OK) {
-            // how many columns of J hold each row (every row of a column of J is in I)
-            wave_cols<false>(
-                S, A, 0, q, wid, lane,
-                [&](int, int row, double) {
-                    const int sl = hfind<LOGH>(S.hk, row);
-                    if (sl >= 0) hinc(S, sl, row); else lookup_fail = true;
-                },
-                [](int) {});
             for (int t = tid; t < nR0; t += NT) {
                 const int row = RR[t];
                 const int sl = hfind<LOGH>(S.hk, row);
@@ -229,21 +220,41 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
         bool kR = S.flag != 0;
         __syncthreads();
 
+        // The entries of J's columns, side by side in slot order: entry u = 64 (wid + NW i) +
+        // lane in this lane's registers i < KE (row, or -1; slot of the row in the hash and
+        // column; value). Entries from KU on are loaded where they are used.
+        int erow[KE], esc[KE];
+        double ev[KE];
+        int total = 0;      // entries of J's columns
+        bool held = false;  // the registers hold them
+        // column, row and value of entry u
+        auto load = [&](int u, int &c, int &row, double &v) {
+            int lo = 0, hi = q - 1;
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (S.pre[mid] <= u) lo = mid; else hi = mid - 1;
+            }
+            c = lo;
+            const int e = S.cbo[lo] + u;
+            row = matrix(Am).rowidx[e];
+            v = matrix(Am).val[e];
+        };
+
         bool first = true, need_solve = true, dropok = false;
         int qmod = -1, mmod = 0;
         int p = 0;
-        if (rec[10] & 2) {
+        if (uni(rec[10]) & 2) {
             // augmented pattern handed over before its solve
-            dropok = (rec[10] & 4) != 0;
-            qmod = rec[11];
-            mmod = rec[12];
+            dropok = (uni(rec[10]) & 4) != 0;
+            qmod = uni(rec[11]);
+            mmod = uni(rec[12]);
         }
         if (status == ST_OK && q == 0 && nRh == 0) {
             // a column whose own rows exceed the register tiers: J = {k}, loop 0
             if (tid == 0) {
                 S.Jl[0] = k;
-                S.cb[0] = A.colptr[k];
-                S.clen[0] = (int)(A.colptr[k + 1] - A.colptr[k]);
+                S.cb[0] = (int)matrix(Am).colptr[k];
+                S.clen[0] = (int)matrix(Am).colptr[k + 1] - S.cb[0];
                 int sl;
                 hinsert<LOGHJ>(S.hJ, k, sl);
             }
@@ -258,30 +269,27 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
             if (nRh > 0) {
                 if (linc) ++l;  // step 6
                 linc = false;
-                int64_t sb[CMAX];
-                int sp[CMAX + 1];
+                int sb[CMAX], sp[CMAX + 1];
                 sp[0] = 0;
 #pragma unroll
                 for (int t = 0; t < CMAX; ++t) {
-                    int64_t b0 = 0, e0 = 0;
+                    int b0 = 0, e0 = 0;
                     if (t < nRh) {
                         const int rt = S.Rh[t];
-                        b0 = A.rowptr[rt];
-                        e0 = A.rowptr[rt + 1];
+                        b0 = (int)matrix(Am).rowptr[rt];
+                        e0 = (int)matrix(Am).rowptr[rt + 1];
                     }
                     sb[t] = b0;
-                    sp[t + 1] = sp[t] + (int)(e0 - b0);
+                    sp[t + 1] = sp[t] + (e0 - b0);
                 }
                 if (tid == 0) S.cnt = 0;
                 __syncthreads();
                 bool ovf = false;
                 for (int u = tid; u < sp[CMAX]; u += NT) {
-                    int64_t b0 = sb[0];
-                    int o0 = 0;
+                    int at = sb[0] + u;
 #pragma unroll
-                    for (int t = 1; t < CMAX; ++t)
-                        if (u >= sp[t]) { b0 = sb[t]; o0 = sp[t]; }
-                    const int col = A.colidx[b0 + (u - o0)];
+                    for (int t = 1; t < CMAX; ++t) at = u >= sp[t] ? sb[t] - sp[t] + u : at;
+                    const int col = matrix(Am).colidx[at];
                     int sl;
                     if (hinsert<LOGHJ>(S.hJ, col, sl)) {
                         const int ps = atomicAdd(&S.cnt, 1);
@@ -291,14 +299,15 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                     }
                 }
                 if (__syncthreads_or(ovf)) { spill = true; break; }
-                p = S.cnt;
+                p = uni(S.cnt);
                 if (tid < p) {
                     const int key = S.newc[tid];
+                    const int b0 = (int)matrix(Am).colptr[key], b1 = (int)matrix(Am).colptr[key + 1];
                     int rank = 0;
                     for (int t = 0; t < p; ++t) rank += (S.newc[t] < key) ? 1 : 0;
                     S.Jl[q + rank] = key;
-                    S.cb[q + rank] = A.colptr[key];
-                    S.clen[q + rank] = (int)(A.colptr[key + 1] - A.colptr[key]);
+                    S.cb[q + rank] = b0;
+                    S.clen[q + rank] = b1 - b0;
                 }
                 need_solve = !(p == 0 && !first);  // empty J-hat: the loop ends without a solve
                 dropok = (p > 0);
@@ -307,24 +316,73 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                 __syncthreads();
             }
             // ================= I-hat: rows of the new columns not in I (step 5)
-            if (need_solve && p > 0) {
-                int total = 0;
-                for (int t = 0; t < p; ++t) total += S.clen[q + t];
-                if (m + total > MM) { spill = true; break; }  // may outgrow the row hash
-                if (tid == 0) S.cnt = 0;
-                __syncthreads();
+            if (need_solve && (p > 0 || first)) {
+                const int qa = q + p;
+                // prefix of the columns' lengths (each wave forms it, and the same words)
+                const int lenl = lane < qa ? S.clen[lane] : 0;
+                const int incl = wscan(lenl, lane), exl = incl - lenl;
+                total = __builtin_amdgcn_readlane(incl, 63);
+                if (m + total - __builtin_amdgcn_readlane(exl, q) > MM) { spill = true; break; }  // may outgrow the row hash
+                if (lane < KE) S.start[wid + NW * lane] = 0ull;
+                if (lane < qa) {
+                    S.pre[lane] = exl;
+                    S.cbo[lane] = S.cb[lane] - exl;
+                }
+                if (lane == 0) S.pre[qa] = total;
+                wave_sync();
+                // (a wave's entries: its own words)
+                if (lane < qa && exl < KU && ((exl >> 6) & (NW - 1)) == wid)
+                    atomicOr(&S.start[exl >> 6], 1ull << (exl & 63));
+                wave_sync();
+#pragma unroll
+                for (int i = 0; i < KE; ++i) {
+                    const int w = wid + NW * i, u = 64 * w + lane;
+                    const bool in = u < total;
+                    // columns that start up to entry u
+                    const int c0 = __popcll(__ballot(lane < qa && exl < 64 * w)) - 1;
+                    const int c = in ? c0 + __popcll(S.start[w] & ((2ull << lane) - 1ull)) : 0;
+                    const int e = in ? S.cbo[c] + u : 0;
+                    const int row = matrix(Am).rowidx[e];
+                    ev[i] = matrix(Am).val[e];
+                    erow[i] = in ? row : -1;
+                    esc[i] = c << 16;
+                }
+                // rows into I; one more holder for the rows of the columns not counted yet
+                const int cinc = first ? 0 : q;
                 int added = 0;
-                wave_cols<false>(
-                    S, A, q, q + p, wid, lane,
-                    [&](int, int row, double) {
-                        int sl;
-                        if (hinsert<LOGH>(S.hk, row, sl)) ++added;
-                        if (sl >= 0) hinc(S, sl, row); else lookup_fail = true;
-                    },
-                    [](int) {});
-                if (added) atomicAdd(&S.cnt, added);
+#pragma unroll
+                for (int b = 0; b < KE; b += 4) {
+                    int key[4];
+                    unsigned sl[4], od[4];
+                    bool fresh[4];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) key[t] = erow[b + t];
+                    hinsert_many<LOGH, 4>(S.hk, key, sl, fresh);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        od[t] = 0u;
+                        const int sh = (int)(sl[t] & 3u) * 8;
+                        if (key[t] >= 0 && (esc[b + t] >> 16) >= cinc)
+                            od[t] = (atomicAdd(&S.hv[sl[t] >> 2], 1u << sh) >> sh) & 0x7Fu;
+                        added += __popcll(__ballot(fresh[t]));
+                        esc[b + t] |= (int)(sl[t] & 0xFFFFu);
+                    }
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        if (od[t] == 1u) now_shared(S, key[t]);
+                }
+                q = qa;  // (load() searches all of J)
+                for (int u = KU + tid; u < total; u += NT) {
+                    int c, row, sl;
+                    double v;
+                    load(u, c, row, v);
+                    added += __popcll(__ballot(hinsert<LOGH>(S.hk, row, sl)));
+                    if (sl < 0) lookup_fail = true;
+                    else if (c >= cinc) hinc(S, sl, row);
+                }
+                if (lane == 0 && added) atomicAdd(&S.madd, added);
                 __syncthreads();
-                m += S.cnt;
+                m += uni(S.madd);
                 if (kR) {
                     // k entered I: its flag moves into the hash entry
                     const int sl = hfind<LOGH>(S.hk, k);
@@ -333,7 +391,7 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                         kR = false;
                     }
                 }
-                q += p;
+                held = total <= KU;
                 p = 0;
             }
             nRh = 0;  // pending rows consumed
@@ -348,42 +406,50 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
             for (int pass = 0; pass < 2 && need_solve && status == ST_OK; ++pass) {
                 const bool reuse = reuse_next;
                 reuse_next = false;
-                // ---- shared rows (held by two or more columns of J), ascending
-                if (tid == 0) {
-                    if (!reuse) { S.nsh = 0; S.kcol = -1; S.akv = 0.0; }
-                    S.flag = 0;
-                }
-                __syncthreads();
-                const bool slovf = S.slovf != 0;
+                // ---- shared rows (held by two or more columns of J), ascending: every row with
+                // two or more holders is in the candidate list (it was shared at the last scan
+                // or reached two holders since), unless that overflowed
+                int nsh;
                 if (reuse) {
-                    // (shared rows already known)
-                } else if (slovf) {
-                    for (int t = tid; t < HS; t += NT) {
-                        const int key = S.hk[t];
-                        if (key != HEMPTY && (hget(S, t) & 0x7Fu) >= 2u) {
-                            const int ps = atomicAdd(&S.nsh, 1);
-                            if (ps < SMAX) S.stmp[ps] = key;
-                        }
-                    }
+                    nsh = uni(S.nsh);
                 } else {
-                    // every row with two or more holders is in the candidate list: it
-                    // was shared at the last scan or reached two holders since
-                    const int nl = S.nsl;
-                    for (int t = tid; t < nl; t += NT) {
-                        const int key = S.slist[t];
-                        const int sl = hfind<LOGH>(S.hk, key);
-                        if (sl >= 0 && (hget(S, sl) & 0x7Fu) >= 2u) {
-                            const int ps = atomicAdd(&S.nsh, 1);
-                            if (ps < SMAX) S.stmp[ps] = key;
+                    const int nl = uni(S.nsl);
+                    const bool slovf = S.slovf != 0;
+                    if (nl <= 64 && !slovf) {
+                        // each wave forms the same list
+                        const int key = lane < nl ? S.slist[lane] : 0;
+                        bool sh = false;
+                        if (lane < nl) {
+                            const int sl = hfind<LOGH>(S.hk, key);
+                            sh = sl >= 0 && (hget(S, sl) & 0x7Fu) >= 2u;
+                        }
+                        const unsigned long long bal = __ballot(sh);
+                        nsh = __popcll(bal);
+                        int rank = 0;
+                        for (unsigned long long b = bal; b; b &= b - 1ull)
+                            rank += __builtin_amdgcn_readlane(key, __ffsll((long long)b) - 1) < key ? 1 : 0;
+                        if (wid == 0 && sh && rank < SMAX) S.srow[rank] = key;
+                    } else {
+                        if (tid == 0) S.nsh = 0;
+                        __syncthreads();
+                        const int nt = slovf ? HS : nl;
+                        for (int t = tid; t < nt; t += NT) {
+                            const int key = slovf ? S.hk[t] : S.slist[t];
+                            const int sl = slovf ? (key != HEMPTY ? t : -1) : hfind<LOGH>(S.hk, key);
+                            if (sl >= 0 && (hget(S, sl) & 0x7Fu) >= 2u) {
+                                const int ps = atomicAdd(&S.nsh, 1);
+                                if (ps < SMAX) S.stmp[ps] = key;
+                            }
+                        }
+                        __syncthreads();
+                        nsh = uni(S.nsh);
+                        if (nsh <= SMAX && tid < nsh) {
+                            const int key = S.stmp[tid];
+                            int rank = 0;
+                            for (int t = 0; t < nsh; ++t) rank += (S.stmp[t] < key) ? 1 : 0;
+                            S.srow[rank] = key;
                         }
                     }
-                }
-                __syncthreads();
-                const int nsh = S.nsh;
-                if (!reuse && !slovf && nsh <= SMAX) {
-                    // the list keeps the shared rows only (no row enters it twice)
-                    for (int t = tid; t < nsh; t += NT) S.slist[t] = S.stmp[t];
-                    if (tid == 0) S.nsl = nsh;
                 }
                 const int ld = q + 1, mp = nsh + q;
                 if (nsh > SMAX || nsh * q > SHV || mp * ld > BLK) {
@@ -396,37 +462,30 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                     pend_mmod = mmod;
                     break;
                 }
-                if (!reuse && tid < nsh) {
-                    const int key = S.stmp[tid];
-                    int rank = 0;
-                    for (int t = 0; t < nsh; ++t) rank += (S.stmp[t] < key) ? 1 : 0;
-                    S.srow[rank] = key;
-                }
-                for (int t = tid; t < mp * ld; t += NT) S.blk[t] = 0.0;
                 if (!reuse) {
                     for (int t = tid; t < nsh * q; t += NT) S.shv[t] = 0.0;
                     for (int t = tid; t < nsh; t += NT) S.shm[t] = 0ull;
-                }
-                __syncthreads();
-                if (reuse) {
-                    // the kept shared values into the block
-                    for (int t = tid; t < nsh * q; t += NT) {
-                        const int si = t / q, c = t - si * q;
-                        S.blk[(q + si) * ld + c] = S.shv[t];
+                    if (tid == 0) { S.kcol = -1; S.akv = 0.0; }
+                    __syncthreads();
+                    // (every wave has read the list and the counts)
+                    if (tid < nsh && S.slovf == 0) S.slist[tid] = S.srow[tid];  // no row enters it twice
+                    if (tid == 0) {
+                        if (S.slovf == 0) S.nsl = nsh;
+                        S.nsh = nsh;
+                        S.flag = 0;
+                        S.madd = 0;
                     }
-                } else
-                // ---- gather: shared entries into the block, private rows into column sums
-                {
-                    auto visit = [&](int c, int row, double v, double &a2) {
-                        const int sl = hfind<LOGH>(S.hk, row);
+                    // ---- gather: shared entries' values; private entries' squares, summed
+                    // per column (8 lanes each, in the entries' order)
+                    auto visit = [&](int u, int c, int row, int sl, double v) {
                         const unsigned cn = sl >= 0 ? (hget(S, sl) & 0x7Fu) : 0u;
+                        double a2 = 0.0;
                         if (cn == 1u) {
-                            a2 += v * v;
+                            a2 = v * v;
                             if (row == k) { S.kcol = c; S.akv = v; }
                         } else if (cn >= 2u) {
                             const int si = sfind(S.srow, nsh, row);
                             if (si >= 0) {
-                                S.blk[(q + si) * ld + c] = v;
                                 S.shv[si * q + c] = v;
                                 atomicOr(&S.shm[si], 1ull << c);
                             } else {
@@ -435,77 +494,98 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                         } else {
                             lookup_fail = true;
                         }
+                        S.blk[u] = a2;
                     };
-                    // HB columns per wave at a time: entries loaded together, then the
-                    // private rows' sums of squares of the HB columns reduced together
-                    constexpr int HB = 8;
-                    for (int cb0 = wid; cb0 < q; cb0 += NW * HB) {
-                        int rr[HB];
-                        double vv[HB], a2[HB];
 #pragma unroll
-                        for (int t = 0; t < HB; ++t) {
-                            const int c = cb0 + NW * t;
-                            rr[t] = -1;
-                            vv[t] = 0.0;
-                            if (c < q && lane < S.clen[c]) {
-                                const int64_t e = S.cb[c] + lane;
-                                rr[t] = A.rowidx[e];
-                                vv[t] = A.val[e];
-                            }
+                    for (int i = 0; i < KE; ++i)
+                        if (erow[i] >= 0)
+                            visit(64 * (wid + NW * i) + lane, esc[i] >> 16, erow[i], esc[i] & 0xFFFF, ev[i]);
+                    for (int base = 0;;) {
+                        __syncthreads();
+                        for (int c = tid >> 3; c < q; c += NT / 8) {
+                            const int lo = max(S.pre[c], base), hi = min(S.pre[c + 1], base + KU);
+                            double x = 0.0;
+                            for (int u = lo + (tid & 7); u < hi; u += 8) x += S.blk[u - base];
+                            x = gsum<8>(x);
+                            if ((tid & 7) == 0) S.s2[c] = (base ? S.s2[c] : 0.0) + x;
                         }
-#pragma unroll
-                        for (int t = 0; t < HB; ++t) {
-                            const int c = cb0 + NW * t;
-                            a2[t] = 0.0;
-                            if (c < q) {
-                                if (rr[t] >= 0) visit(c, rr[t], vv[t], a2[t]);
-                                const int len = S.clen[c];
-                                if (len > 64) {
-                                    const int64_t e0 = S.cb[c];
-                                    for (int u = 64 + lane; u < len; u += 64) visit(c, A.rowidx[e0 + u], A.val[e0 + u], a2[t]);
-                                }
-                            }
-                        }
-#pragma unroll
-                        for (int t = 0; t < HB; ++t) {
-                            const int c = cb0 + NW * t;
-                            if (c < q) {
-                                const double x = wsum(a2[t]);
-                                if (lane == 0) S.s2[c] = x;
-                            }
+                        __syncthreads();
+                        base += KU;
+                        if (base >= total) break;
+                        // the next KU entries, loaded again
+                        for (int u = base + tid; u < min(total, base + KU); u += NT) {
+                            int c, row;
+                            double v;
+                            load(u, c, row, v);
+                            visit(u - base, c, row, hfind<LOGH>(S.hk, row), v);
                         }
                     }
                 }
-                __syncthreads();
                 // ---- the row of row k: shared (right-hand side 1), private (compressed), or
                 // outside the pattern (a constant 1 in ||r||^2). Private in column j: the
                 // collapsed row carries beta = a_kj / s_j and ||r||^2 gains 1 - beta^2.
-                const int ksl = hfind<LOGH>(S.hk, k);
-                const int kcn = ksl >= 0 ? (int)(hget(S, ksl) & 0x7Fu) : -1;
+                const int ksl = uni(hfind<LOGH>(S.hk, k));
+                const int kcn = ksl >= 0 ? uni((int)(hget(S, ksl) & 0x7Fu)) : -1;
                 double kconst = (kcn <= 0) ? 1.0 : 0.0;
                 if (kcn == 1 && S.kcol >= 0) {
                     const double sk = sqrt(S.s2[S.kcol]);
                     const double bk = sk > 0.0 ? S.akv / sk : 0.0;
                     kconst = fmax(0.0, 1.0 - bk * bk);
                 }
-                // rows 0..q-1: the collapsed private rows (diagonal), rows q..q+S-1: shared
-                if (tid < q) {
-                    const double sj = sqrt(S.s2[tid]);
-                    S.blk[tid * ld + tid] = sj;
-                    if (kcn == 1 && S.kcol == tid && sj > 0.0) S.blk[tid * ld + q] = S.akv / sj;
+                // the collapsed row's right-hand side, and the shared row of k
+                double rk = 0.0;
+                if (kcn == 1 && S.kcol >= 0) {
+                    const double sj = sqrt(S.s2[S.kcol]);
+                    if (sj > 0.0) rk = S.akv / sj;
                 }
-                if (kcn >= 2 && tid == 0) {
-                    const int si = sfind(S.srow, nsh, k);
-                    if (si >= 0) S.blk[(q + si) * ld + q] = 1.0;
+                const int kc = (kcn == 1) ? uni(S.kcol) : -1;
+                const int ksi = (kcn >= 2) ? uni(sfind(S.srow, nsh, k)) : -1;
+                if (nsh > SU) {
+                    // rows 0..q-1: the collapsed private rows (diagonal), rows q..q+S-1: shared
+                    for (int t = tid; t < q * ld; t += NT) {
+                        const int i = t / ld, c = t - i * ld;
+                        S.blk[t] = i == c ? sqrt(S.s2[c]) : (c == q && i == kc) ? rk : 0.0;
+                    }
+                    for (int t = tid; t < nsh * ld; t += NT) {
+                        const int si = t / ld, c = t - si * ld;
+                        S.blk[q * ld + t] = c < q ? S.shv[si * q + c] : si == ksi ? 1.0 : 0.0;
+                    }
+                    __syncthreads();
                 }
-                __syncthreads();
                 // ---- Householder QR of the compressed block and Q^T e (wave 0: lane c
                 // holds column c, lane q the right-hand side). Column j has nonzeros only
                 // in row j and the shared rows (the reflectors of earlier columns touch
                 // exactly those rows), so each reflector has 1 + S entries.
                 if (wid == 0) {
                     bool singular = false;
-                    constexpr int SU = 8;
+                    // back substitution over the columns cm: lane i holds (Q^T e)_i; m_j
+                    // broadcast by readlane (the divisions by the diagonal prepared
+                    // beforehand, a lane each; the next column's entries loaded ahead)
+                    auto back_substitute = [&](unsigned long long left) {
+                        const bool in = (left >> lane) & 1ull;
+                        double y = in ? S.blk[lane * ld + q] : 0.0;
+                        const double rdl = in ? S.rd[lane] : 1.0;
+                        const double ril = 1.0 / rdl;
+                        double mine = 0.0;
+                        auto rcol = [&](int j) { return (in && lane < j) ? S.blk[lane * ld + j] : 0.0; };
+                        int j = left ? 63 - __clzll((long long)left) : 0;
+                        double rj = left ? rcol(j) : 0.0;
+                        while (left) {
+                            left ^= 1ull << j;
+                            const int jn = left ? 63 - __clzll((long long)left) : 0;
+                            const double rjn = left ? rcol(jn) : 0.0;
+                            const double mj =
+                                div_by(readlane_f64(y, j), readlane_f64(rdl, j), readlane_f64(ril, j));
+                            if (lane == j) mine = mj;
+                            y -= rj * mj;
+                            j = jn;
+                            rj = rjn;
+                        }
+                        return mine;
+                    };
+                    // columns that take a step of the two loops below; all of them where a
+                    // factor is kept, which is written row by row
+                    unsigned long long cm = (1ull << q) - 1ull;
                     // Few shared rows: lane c keeps the shared-row entries of column c in
                     // registers; the reflector of step j is read from lane j. Row j of
                     // column c > j is zero before step j, except the right-hand side of
@@ -514,15 +594,58 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                     // The slots past nsh hold zeros, but the two instances fuse their
                     // sums of products differently, so their results agree only to
                     // rounding level, not bit for bit.
+                    //
+                    // The columns of J-hat are those of a few dominant rows, so most meet the
+                    // others in one shared row only. The columns c with one entry b_c in the
+                    // shared rows, all in row t, are eliminated together, before the others:
+                    // their q reflectors leave row t scaled by 1 / sqrt(T), T = 1 + sum of
+                    // (b_c / s_c)^2, and given the other columns' part f of row t's right-hand
+                    // side they have m_c = (b_c / s_c^2) z, z = f / T (k private in one of
+                    // them: d = its right-hand side, f less d b / s, and m = (d (T - (b / s)^2)
+                    // + f b / s) / (T s), T - (b / s)^2 summed without it). What is left takes
+                    // the steps: 1.2k cycles each, q = 17 of them before the drop, about 3 now.
                     auto qr_regs = [&](auto ns) {
                         constexpr int SU = decltype(ns)::value;
                         double b[SU];
+                        int own = -1, nown = 0;  // the last shared row of this lane's column, their number
 #pragma unroll
-                        for (int t = 0; t < SU; ++t) b[t] = (lane <= q && t < nsh) ? S.blk[(q + t) * ld + lane] : 0.0;
-                        const double sjl = (lane < q) ? S.blk[lane * ld + lane] : 0.0;
-                        const int kc = (kcn == 1) ? S.kcol : -1;
-                        const double rk = (kc >= 0) ? S.blk[kc * ld + q] : 0.0;
-                        for (int j = 0; j < q; ++j) {
+                        for (int t = 0; t < SU; ++t) {
+                            b[t] = (lane < q && t < nsh) ? S.shv[t * q + lane] : 0.0;
+                            if (b[t] != 0.0) {
+                                own = t;
+                                ++nown;
+                            }
+                            if (lane == q && t == ksi) b[t] = 1.0;
+                        }
+                        const bool inq = lane < q;
+                        const double sjl = inq ? sqrt(S.s2[lane]) : 0.0;
+                        double bo = 0.0;
+#pragma unroll
+                        for (int t = 0; t < SU; ++t) bo = own == t ? b[t] : bo;
+                        const bool alone = inq && !whole && nown <= 1 && sjl > 0.0 && sjl <= DBL_MAX &&
+                                           fabs(bo) <= 1e60 * sjl;
+                        cm = __ballot(inq && !alone);
+                        const double ci = alone ? bo / sjl : 0.0;
+                        const bool kin = kc >= 0 && !((cm >> kc) & 1ull);  // k private in one of them
+                        const double ck = kin ? readlane_f64(ci, kc) : 0.0;
+                        double Tl = 1.0, Tx = 1.0;  // T of this lane's row, without the column of k
+#pragma unroll
+                        for (int t = 0; t < SU; ++t) {
+                            if (t >= nsh || whole) continue;
+                            const double x = 1.0 + wsum(own == t && lane != kc ? ci * ci : 0.0);
+                            const bool kt = kin && __builtin_amdgcn_readlane(own, kc) == t;
+                            const double T = kt ? x + ck * ck : x;
+                            if (own == t) {
+                                Tl = T;
+                                Tx = x;
+                            }
+                            // the other columns and the right-hand side (lane q)
+                            if (lane == q && kt) b[t] = -ck * rk;
+                            if (!alone) b[t] *= 1.0 / sqrt(T);
+                        }
+                        bool sing = false;
+                        for (unsigned long long left = cm; left; left &= left - 1ull) {
+                            const int j = __ffsll((long long)left) - 1;
                             double u[SU];
 #pragma unroll
                             for (int t = 0; t < SU; ++t) u[t] = readlane_f64(b[t], j);
@@ -537,8 +660,8 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                             hh_scalars(s0 + s1, x0, nx, be);
                             const double alpha = (x0 >= 0.0) ? -nx : nx;
                             const double v0 = x0 - alpha;
-                            if (!(nx > 0.0)) singular = true;
-                            if (lane > j && lane <= q) {
+                            if (!(nx > 0.0)) sing = true;
+                            if (lane > j && lane <= q && !alone) {
                                 const double bj = (lane == q && j == kc) ? rk : 0.0;
                                 double w0 = v0 * bj, w1 = 0.0;
 #pragma unroll
@@ -559,6 +682,28 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                         for (int t = 0; t < SU; ++t) r2 += b[t] * b[t];
                         r2 = readlane_f64(r2, q);
                         if (lane == 0) S.rn = sqrt(r2 + kconst);
+                        wave_sync();
+                        singular = sing;
+                        if (sing) return;
+                        double mine = back_substitute(cm);
+                        if (cm != (1ull << q) - 1ull) {
+                            // the others, from what those leave of their row
+                            double f = 0.0;
+#pragma unroll
+                            for (int t = 0; t < SU; ++t) {
+                                if (t >= nsh) continue;
+                                const double bt = inq && !alone ? S.shv[t * q + lane] : 0.0;
+                                const double x = (t == ksi ? 1.0 : 0.0) - wsum(bt * mine);
+                                if (own == t) f = x;
+                            }
+                            if (alone) {
+                                const bool kl = lane == kc;
+                                const double d = kl ? rk : 0.0;
+                                const double fk = (kin && !kl && own == __builtin_amdgcn_readlane(own, kc)) ? f - ck * rk : f;
+                                mine = (d * Tx + ci * fk) / Tl / sjl;
+                            }
+                        }
+                        if (inq) S.mt[lane] = mine;
                     };
                     if (nsh <= 4) {
                         qr_regs(std::integral_constant<int, 4>{});
@@ -623,26 +768,13 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                     }
                     r2 = wsum(r2);
                     if (lane == 0) S.rn = sqrt(r2 + kconst);
-                    }
                     wave_sync();
                     if (!singular) {
-                        // back substitution: lane i holds (Q^T e)_i; m_j broadcast by readlane
-                        // (the divisions by the diagonal done beforehand, a lane each)
-                        double y = (lane < q) ? S.blk[lane * ld + q] : 0.0;
-                        const double rdl = (lane < q) ? S.rd[lane] : 1.0;
-                        const double ril = 1.0 / rdl;
-                        double mine = 0.0;
-                        for (int j = q - 1; j >= 0; --j) {
-                            const double rj = (lane < j) ? S.blk[lane * ld + j] : 0.0;
-                            const double mj =
-                                div_by(readlane_f64(y, j), readlane_f64(rdl, j), readlane_f64(ril, j));
-                            if (lane == j) mine = mj;
-                            y -= rj * mj;
-                        }
+                        const double mine = back_substitute(cm);
                         if (lane < q) S.mt[lane] = mine;
-                    } else if (lane == 0) {
-                        S.flag = 1;
                     }
+                    }
+                    if (singular && lane == 0) S.flag = 1;
                 }
                 __syncthreads();
                 if (S.flag) { status = ST_SINGULAR; break; }
@@ -652,7 +784,7 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                 if (pass == 0 && dropok && P.drop != DROP_NONE) {
                     const double th = (P.drop == DROP_FIXED)
                                           ? P.tol
-                                          : P.eps / ((double)q * __longlong_as_double((long long)*A.norm1_bits));
+                                          : P.eps / ((double)q * __longlong_as_double((long long)*matrix(Am).norm1_bits));
                     // kept columns as a lane mask (q <= 63: one lane per column, each wave
                     // forms the same mask); with none above the threshold, the largest |m_j|
                     // stays (the smaller column index on ties)
@@ -673,14 +805,94 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                         keepm = __ballot(inq && jg == bg);
                     }
                     if (nk < q) {
-                        // rows of the dropped columns lose one holder
-                        wave_cols_if<false>(
-                            S, A, 0, q, wid, lane,
-                            [&](int, int row, double) {
-                                const int sl = hfind<LOGH>(S.hk, row);
-                                if (sl >= 0) hdec(S, sl); else lookup_fail = true;
-                            },
-                            [](int) {}, [&](int c) { return ((keepm >> c) & 1ull) == 0ull; });
+                        // rows of the dropped columns lose one holder; the others keep their
+                        // entries under their column's new slot
+                        auto slot = [&](int c) { return __popcll(keepm & ((1ull << c) - 1ull)); };
+#pragma unroll
+                        for (int i = 0; i < KE; ++i) {
+                            const int c = esc[i] >> 16;
+                            if (erow[i] < 0) continue;
+                            if ((keepm >> c) & 1ull) {
+                                esc[i] = (esc[i] & 0xFFFF) | (slot(c) << 16);
+                            } else {
+                                hdec(S, esc[i] & 0xFFFF);
+                                erow[i] = -1;
+                            }
+                        }
+                        for (int u = KU + tid; u < total; u += NT) {
+                            int c, row;
+                            double v;
+                            load(u, c, row, v);
+                            if ((keepm >> c) & 1ull) continue;
+                            const int sl = hfind<LOGH>(S.hk, row);
+                            if (sl >= 0) hdec(S, sl); else lookup_fail = true;
+                        }
+                        if (nsh <= SU) {
+                            // few shared rows: the first wave makes the compressed data of the
+                            // kept columns (as below), lane c for column c
+                            if (wid == 0) {
+                                const int qn = __popcll(keepm), d = slot(lane);
+                                const bool kept = inq && ((keepm >> lane) & 1ull);
+                                double b[SU], acc = inq ? S.s2[lane] : 0.0, ka = 0.0;
+                                int kcn2 = -1, jl = 0, cl = 0, cbv = 0;
+#pragma unroll
+                                for (int t = 0; t < SU; ++t) b[t] = (inq && t < nsh) ? S.shv[t * q + lane] : 0.0;
+                                if (kept) {
+                                    jl = S.Jl[lane];
+                                    cl = S.clen[lane];
+                                    cbv = S.cb[lane];
+                                }
+                                if (kc >= 0 && ((keepm >> kc) & 1ull)) {
+                                    kcn2 = slot(kc);
+                                    ka = S.akv;
+                                }
+#pragma unroll
+                                for (int t = 0; t < SU; ++t) {
+                                    if (t >= nsh) continue;
+                                    const unsigned long long hm = S.shm[t] & keepm;
+                                    if (hm == (1ull << lane)) acc += b[t] * b[t];
+                                    if (t == ksi && __popcll(hm) == 1) {
+                                        const int c = __ffsll((long long)hm) - 1;
+                                        kcn2 = slot(c);
+                                        ka = readlane_f64(b[t], c);
+                                    }
+                                }
+                                for (int t = lane; t < HJ; t += 64) S.hJ[t] = HEMPTY;
+                                wave_sync();
+                                int ns = 0;
+#pragma unroll
+                                for (int t = 0; t < SU; ++t) {
+                                    if (t >= nsh || __popcll(S.shm[t] & keepm) < 2) continue;
+                                    if (kept) S.shv[ns * qn + d] = b[t];
+                                    if (lane == 0) {
+                                        const int row = S.srow[t];
+                                        S.srow[ns] = row;
+                                        if (S.slovf == 0) S.slist[ns] = row;
+                                    }
+                                    ++ns;
+                                }
+                                if (kept) {
+                                    S.s2[d] = acc;
+                                    S.Jl[d] = jl;
+                                    S.cb[d] = cbv;
+                                    S.clen[d] = cl;
+                                    int sl;
+                                    hinsert<LOGHJ>(S.hJ, jl, sl);
+                                }
+                                if (lane == 0) {
+                                    S.kcol = kcn2;
+                                    S.akv = ka;
+                                    S.nsh = ns;
+                                    if (S.slovf == 0) S.nsl = ns;
+                                }
+                            }
+                            held = total <= KU;
+                            q = __popcll(keepm);
+                            qmod = 0;
+                            reuse_next = true;
+                            __syncthreads();
+                            continue;  // solve on the kept pattern
+                        }
                         __syncthreads();
                         // the kept columns' compressed data for the re-solve (old slots
                         // here): a shared row keeps its place among the rows still held by
@@ -690,7 +902,6 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                         {
                             const int qo = q, nso = nsh;
                             const int qn = __popcll(keepm);
-                            auto slot = [&](int c) { return __popcll(keepm & ((1ull << c) - 1ull)); };
                             if (wid == 0) {
                                 int base = 0;
                                 for (int s0 = 0; s0 < nso; s0 += 64) {
@@ -702,14 +913,14 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                                 }
                                 if (lane == 0) S.nsh2 = base;
                             }
-                            int kc = -1;
+                            int kc2 = -1;
                             double ka = 0.0;
                             if (tid == 0) {
                                 const int ksl2 = hfind<LOGH>(S.hk, k);
                                 const unsigned kcn2 = ksl2 >= 0 ? (hget(S, ksl2) & 0x7Fu) : 0u;
                                 if (kcn2 == 1u) {
                                     if (S.kcol >= 0 && ((keepm >> S.kcol) & 1ull)) {
-                                        kc = slot(S.kcol);
+                                        kc2 = slot(S.kcol);
                                         ka = S.akv;
                                     } else {
                                         const int si = sfind(S.srow, nso, k);
@@ -717,7 +928,7 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                                             const unsigned long long hm = S.shm[si] & keepm;
                                             if (__popcll(hm) == 1) {
                                                 const int c = __ffsll((long long)hm) - 1;
-                                                kc = slot(c);
+                                                kc2 = slot(c);
                                                 ka = S.shv[si * qo + c];
                                             }
                                         }
@@ -750,7 +961,7 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                             for (int t = tid; t < nsn * qn; t += NT) S.shv[t] = S.blk[t];
                             if (tid < qn) S.s2[tid] = S.rd[tid];
                             if (tid == 0) {
-                                S.kcol = kc;
+                                S.kcol = kc2;
                                 S.akv = ka;
                                 S.nsh = nsn;
                             }
@@ -764,17 +975,16 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                         if (wid == 0) {
                             // compaction of the slots in order: lane c moves to the number of
                             // kept slots below it
-                            const bool kc = inq && ((keepm >> lane) & 1ull);
-                            int jl = 0, cl = 0;
-                            int64_t cbv = 0;
-                            if (kc) {
+                            const bool kept = inq && ((keepm >> lane) & 1ull);
+                            int jl = 0, cl = 0, cbv = 0;
+                            if (kept) {
                                 jl = S.Jl[lane];
                                 cbv = S.cb[lane];
                                 cl = S.clen[lane];
                             }
                             const int d = __popcll(keepm & ((1ull << lane) - 1ull));
                             wave_sync();
-                            if (kc) {
+                            if (kept) {
                                 S.Jl[d] = jl;
                                 S.cb[d] = cbv;
                                 S.clen[d] = cl;
@@ -783,7 +993,7 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                         }
                         for (int t = tid; t < HJ; t += NT) S.hJ[t] = HEMPTY;
                         __syncthreads();
-                        q = S.cnt;
+                        q = uni(S.cnt);
                         for (int c = tid; c < q; c += NT) {
                             int sl;
                             hinsert<LOGHJ>(S.hJ, S.Jl[c], sl);
@@ -803,7 +1013,7 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
             if (rn <= P.eps || l >= P.lmax) break;
 
             // ================= dominant rows of r = A(I,J) m - e_k (step 4)
-            const int nsh = S.nsh;
+            const int nsh = uni(S.nsh);
             if (tid < q) {
                 const int jc = S.Jl[tid];
                 int rank = 0;
@@ -842,17 +1052,34 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                 if (ri != 0.0 && sl >= 0 && !(hget(S, sl) & 0x80u)) offer(fabs(ri), row);
             }
             // private rows: one product each
-            wave_cols<true>(
-                S, A, 0, q, wid, lane,
-                [&](int c, int row, double v) {
-                    const int sl = hfind<LOGH>(S.hk, row);
-                    const unsigned hvv = sl >= 0 ? hget(S, sl) : 0u;
-                    if ((hvv & 0x7Fu) == 1u && !(hvv & 0x80u)) {
-                        const double ri = __fma_rn(v, S.mt[c], 0.0) - ((row == k) ? 1.0 : 0.0);
-                        if (ri != 0.0) offer(fabs(ri), row);
-                    }
-                },
-                [](int) {});
+            auto product = [&](int c, int row, int sl, double v) {
+                const unsigned hvv = sl >= 0 ? hget(S, sl) : 0u;
+                if ((hvv & 0x7Fu) == 1u && !(hvv & 0x80u)) {
+                    const double ri = __fma_rn(v, S.mt[c], 0.0) - ((row == k) ? 1.0 : 0.0);
+                    if (ri != 0.0) offer(fabs(ri), row);
+                }
+            };
+            if (held) {
+#pragma unroll
+                for (int i = 0; i < KE; ++i)
+                    if (erow[i] >= 0) product(esc[i] >> 16, erow[i], esc[i] & 0xFFFF, ev[i]);
+            } else {
+                // more entries than the registers hold, and their columns may have moved
+                const int lenl = lane < q ? S.clen[lane] : 0;
+                const int incl = wscan(lenl, lane);
+                if (lane < q) {
+                    S.pre[lane] = incl - lenl;
+                    S.cbo[lane] = S.cb[lane] - (incl - lenl);
+                }
+                const int tq = __builtin_amdgcn_readlane(incl, 63);
+                wave_sync();
+                for (int u = tid; u < tq; u += NT) {
+                    int c, row;
+                    double v;
+                    load(u, c, row, v);
+                    product(c, row, hfind<LOGH>(S.hk, row), v);
+                }
+            }
             // row k outside the columns of J: r(k) = -1
             if (tid == 0) {
                 const int ksl = hfind<LOGH>(S.hk, k);
@@ -903,22 +1130,22 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
             nRh = nsel;
             linc = true;
         }
-        if (lookup_fail) atomicOr(args.err, 16);
+        if (lookup_fail) atomicOr(kargs().err, 16);
 
         if (spill) {
             // ---- hand the column over to a later class: the next one, or for a block
             // that did not fit, the first level with a larger block, or the dense class
             // when most of its rows are shared
-            int32_t *qo = args.rec_out, *qc = args.rec_out_count;
-            int qs = args.rec_out_stride;
-            int64_t qcap = args.rec_out_cap;
+            int32_t *qo = kargs().rec_out, *qc = kargs().rec_out_count;
+            int qs = kargs().rec_out_stride;
+            int64_t qcap = kargs().rec_out_cap;
             if (blk_nsh >= 0) {
-                const int d = (args.rec_alt[1] != nullptr && 2 * blk_nsh >= m) ? 1 : (args.rec_alt[0] != nullptr ? 0 : -1);
+                const int d = (kargs().rec_alt[1] != nullptr && 2 * blk_nsh >= m) ? 1 : (kargs().rec_alt[0] != nullptr ? 0 : -1);
                 if (d >= 0) {
-                    qo = args.rec_alt[d];
-                    qc = args.rec_alt_count[d];
-                    qs = args.rec_alt_stride[d];
-                    qcap = args.rec_alt_cap[d];
+                    qo = kargs().rec_alt[d];
+                    qc = kargs().rec_alt_count[d];
+                    qs = kargs().rec_alt_stride[d];
+                    qcap = kargs().rec_alt_cap[d];
                 }
             }
             if (tid == 0) {
@@ -965,41 +1192,41 @@ __global__ __launch_bounds__(NT, WPC) void wide_kernel(WideArgs args) {
                 continue;
             }
             status = ST_CAP;  // no room in the next class
-            if (tid == 0 && qo != nullptr) atomicOr(args.err, 32);  // queue full
+            if (tid == 0 && qo != nullptr) atomicOr(kargs().err, 32);  // queue full
         }
 
         // ---------------------------------------------------------- output (rows ascending)
         const int qq = (status == ST_OK) ? q : 0;
-        const int64_t slot = args.arena_base + (int64_t)ucol * 64;
+        const int64_t slot = kargs().arena_base + (int64_t)ucol * 64;
         for (int c = tid; c < qq; c += NT) {
             const int jc = S.Jl[c];
             int rank = 0;
             for (int t = 0; t < qq; ++t) rank += (S.Jl[t] < jc) ? 1 : 0;
-            args.out.arenaJ[slot + rank] = jc;
-            args.out.arenaV[slot + rank] = S.mt[c];
+            kargs().out.arenaJ[slot + rank] = jc;
+            kargs().out.arenaV[slot + rank] = S.mt[c];
         }
         if (tid == 0) {
-            args.out.off[ucol] = slot;
-            args.out.nJ[ucol] = qq;
-            args.out.nI[ucol] = m;
-            args.out.loops[ucol] = l;
-            args.out.status[ucol] = status;
-            args.out.resnorm[ucol] = rn;
-            args.out.flops[ucol] = fl;
+            kargs().out.off[ucol] = slot;
+            kargs().out.nJ[ucol] = qq;
+            kargs().out.nI[ucol] = m;
+            kargs().out.loops[ucol] = l;
+            kargs().out.status[ucol] = status;
+            kargs().out.resnorm[ucol] = rn;
+            kargs().out.flops[ucol] = fl;
         }
-        if (args.out.fac != nullptr) {
+        if (kargs().out.fac != nullptr) {
             // R of the final (compressed) solve: R^T R = A(I,J)^T A(I,J); rows 0..q-1 of
             // the block hold its strict upper part, rd the diagonal
             if (tid == 0) {
-                const long long fo = (qq > 0) ? fac_reserve(args.out, qq) : -1LL;
-                args.out.foff[ucol] = fo;
+                const long long fo = (qq > 0) ? fac_reserve(kargs().out, qq) : -1LL;
+                kargs().out.foff[ucol] = fo;
                 S.cnt = (int)(fo & 0xffffffffLL);
                 S.nsh = (int)(fo >> 32);
             }
             __syncthreads();
             const long long fo = ((long long)S.nsh << 32) | (long long)(unsigned)S.cnt;
             if (fo >= 0) {
-                double *F = args.out.fac + fo;
+                double *F = kargs().out.fac + fo;
                 const int ld = qq + 1;
                 for (int c = tid; c < qq; c += NT) F[c] = (double)S.Jl[c];
                 for (int t = tid; t < qq * qq; t += NT) {
@@ -1016,12 +1243,18 @@ namespace {
 // Level 2 takes level 0's columns whose compressed block does not fit (many shared
 // rows, as in the columns that pick a relatively dense row) at two workgroups per CU
 // instead of sending them to the one-per-CU level 3.
+// Threads: two waves in level 0, whose columns have about 600 entries (256 registers a lane
+// against 128 and scratch spills with four waves: a build of 400 000 columns 16.8 against
+// 17.1 ms); four in level 1, with 1024 to 2048 entries (16.8 against 17.4 ms with two).
 constexpr int kWideLogH[WIDE_LEVELS] = {11, 12, 11, 14};
+constexpr int kWideNT[WIDE_LEVELS] = {128, 256, 256, 256};
 constexpr int kWidePerCU[WIDE_LEVELS] = {4, 3, 2, 1};
-#define RSAI_WIDE0 kWideLogH[0], 2048, 768, 128, kWidePerCU[0]
-#define RSAI_WIDE1 kWideLogH[1], 2048, 768, 128, kWidePerCU[1]
-#define RSAI_WIDE2 kWideLogH[2], 4096, 1536, 128, kWidePerCU[2]
-#define RSAI_WIDE3 kWideLogH[3], 6144, 1536, 256, kWidePerCU[3]
+// KE: the registers hold as many entries as the level's rows, up to 4096
+#define RSAI_WIDE(L, BLK, SHV, SMAX, KE) kWideNT[L], kWideLogH[L], BLK, SHV, SMAX, KE / kWideNT[L], kWidePerCU[L]
+#define RSAI_WIDE0 RSAI_WIDE(0, 2048, 768, 128, 1024)
+#define RSAI_WIDE1 RSAI_WIDE(1, 2048, 768, 128, 2048)
+#define RSAI_WIDE2 RSAI_WIDE(2, 4096, 1536, 128, 2048)
+#define RSAI_WIDE3 RSAI_WIDE(3, 6144, 1536, 256, 4096)
 }  // namespace
 
 int wide_max_rows(int level) { return (1 << kWideLogH[level]) / 2; }
@@ -1034,14 +1267,15 @@ int wide_queue_stride(int queue) {
 int wide_blocks_per_cu(int level) { return kWidePerCU[level]; }
 
 void launch_wide_kernel(int level, const WideArgs &a, int blocks, hipStream_t s) {
+    const dim3 nt(kWideNT[level]);
     if (level == 0)
-        hipLaunchKernelGGL((wide_kernel<RSAI_WIDE0>), dim3(blocks), dim3(NT), 0, s, a);
+        hipLaunchKernelGGL((wide_kernel<RSAI_WIDE0>), dim3(blocks), nt, 0, s, a);
     else if (level == 1)
-        hipLaunchKernelGGL((wide_kernel<RSAI_WIDE1>), dim3(blocks), dim3(NT), 0, s, a);
+        hipLaunchKernelGGL((wide_kernel<RSAI_WIDE1>), dim3(blocks), nt, 0, s, a);
     else if (level == 2)
-        hipLaunchKernelGGL((wide_kernel<RSAI_WIDE2>), dim3(blocks), dim3(NT), 0, s, a);
+        hipLaunchKernelGGL((wide_kernel<RSAI_WIDE2>), dim3(blocks), nt, 0, s, a);
     else
-        hipLaunchKernelGGL((wide_kernel<RSAI_WIDE3>), dim3(blocks), dim3(NT), 0, s, a);
+        hipLaunchKernelGGL((wide_kernel<RSAI_WIDE3>), dim3(blocks), nt, 0, s, a);
 }
 
 }  // namespace rsai
