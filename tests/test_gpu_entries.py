@@ -50,3 +50,24 @@ def test_malformed(N, where):
         B = gen.CSC(A.n, A.colptr, r, A.val)
         with pytest.raises(rsai.RSAIError, match="flags 2"):
             rsai.build(rsai.Matrix.from_host(B), c=3, lmax=4, eps=0.4)
+
+
+@pytest.mark.parametrize("n,lengths", [(1, (1,)), (63, (7, 8, 9)), (64, (0, 1, 16, 17)), (65, (3,)), (513, (200, 1, 0)),
+                                       (4097, (7, 8, 0, 9))])
+def test_spmv(n, lengths):
+    """y = A x and A^T x: rows around the eight lanes of a group, empty ones, groups and
+    workgroups that end past the last row. Error bound: the sum of |a_ij x_j| times the
+    roundings of a sum of that many products."""
+    import torch
+    import paper_1503_04500_amd.rsai as rsai
+    A = _matrix(n, [min(k, n) for k in lengths], seed=n + 1)
+    x = np.random.default_rng(n).standard_normal(n)
+    dA, dx = rsai.Matrix.from_host(A), torch.from_numpy(x).cuda()
+    col = A.col_of_entry()
+    for transpose, out, src in ((False, A.rowidx, col), (True, col, A.rowidx)):
+        want, mag = np.zeros(n, np.longdouble), np.zeros(n)
+        np.add.at(want, out, A.val.astype(np.longdouble) * x[src])
+        np.add.at(mag, out, np.abs(A.val * x[src]))
+        terms = np.bincount(out, minlength=n)
+        y = dA.spmv(dx, transpose=transpose).cpu().numpy()
+        assert np.all(np.abs(y - want) <= (terms + 1) * 2.0 ** -53 * mag)
