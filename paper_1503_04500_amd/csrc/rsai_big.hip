@@ -45,7 +45,7 @@ struct BigLds {
     double rd[BQMAX_BIG];
     double bt[BQMAX_BIG];
     double red[NW * 8];
-    double redp[NW * (NB + 1)];    // per-wave partials of the register-panel reductions
+    double redp[2][NW * (NB + 1)];    // per-wave partials of the register-panel reductions
     double Tm[16 * 16];            // T of the compact WY form of a panel
     double Wp[16 * NCTMAX * 16];   // T^T V^T C of a panel
     int ired[NW * 2];
@@ -60,10 +60,8 @@ int big_max_cols() { return BQMAX_BIG; }
 
 // block-wide sum (every thread gets the result)
 __device__ __forceinline__ double bsum(double x, BigLds &S) {
-    x = gsum<16>(x);
+    x = gsum<64>(x);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    x += __shfl_xor(x, 16);
-    x += __shfl_xor(x, 32);
     __syncthreads();
     if (lane == 0) S.dred[w] = x;
     __syncthreads();
@@ -226,28 +224,25 @@ __device__ void panel_update(double *B, int64_t ld, double *y, int m, int qn, in
 }
 
 // Block-wide sums of x[LO..HI) (up to NB + 1 values): a wave-level tree per value,
-// then the four waves' partials through LDS. Every thread gets the totals.
-template <int LO, int HI>
+// then the four waves' partials through LDS. Every thread gets the totals. Two calls in
+// turn use BUF 0 and 1, so that each needs one barrier: the other call's lies between a
+// buffer's reads and its next writes.
+template <int LO, int HI, int BUF>
 __device__ __forceinline__ void bsum_many(double (&x)[NB + 1], BigLds &S) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
-    for (int u = LO; u < HI; ++u) {
-        x[u] = gsum<16>(x[u]);
-        x[u] += __shfl_xor(x[u], 16);
-        x[u] += __shfl_xor(x[u], 32);
-    }
+    for (int u = LO; u < HI; ++u) x[u] = gsum<64>(x[u]);
     if (lane == 0)
 #pragma unroll
-        for (int u = LO; u < HI; ++u) S.redp[w * (NB + 1) + u] = x[u];
+        for (int u = LO; u < HI; ++u) S.redp[BUF][w * (NB + 1) + u] = x[u];
     __syncthreads();
 #pragma unroll
     for (int u = LO; u < HI; ++u) {
         double t = 0.0;
 #pragma unroll
-        for (int ww = 0; ww < NW; ++ww) t += S.redp[ww * (NB + 1) + u];
+        for (int ww = 0; ww < NW; ++ww) t += S.redp[BUF][ww * (NB + 1) + u];
         x[u] = t;
     }
-    __syncthreads();
 }
 
 // One step of the register panel: the reflector of panel column UJ (block column
@@ -267,7 +262,7 @@ __device__ __forceinline__ void panel_step(double (&pv)[RPT][NB], int m, int p0,
         if (r >= j && r < m) x[0] += pv[i][UJ] * pv[i][UJ];
         if (r == j) x[1] = pv[i][UJ];
     }
-    bsum_many<0, 2>(x, S);
+    bsum_many<0, 2, 0>(x, S);
     const double x0 = x[1];
     double nx, be;
     hh_scalars(x[0], x0, nx, be);
@@ -293,7 +288,7 @@ __device__ __forceinline__ void panel_step(double (&pv)[RPT][NB], int m, int p0,
 #pragma unroll
                 for (int i = 0; i < RPT; ++i) d[u] += v[i] * pv[i][u];
             }
-            bsum_many<UJ + 1, NB>(d, S);
+            bsum_many<UJ + 1, NB, 1>(d, S);
 #pragma unroll
             for (int u = UJ + 1; u < NB; ++u) {
                 const double f = d[u] * be;

@@ -118,12 +118,7 @@ __device__ __forceinline__ CArgs &kargs() {
 }
 
 // wave-wide sum; every lane gets the bitwise-same value
-__device__ __forceinline__ double wsum(double x) {
-    x = gsum<16>(x);
-    x += __shfl_xor(x, 16);
-    x += __shfl_xor(x, 32);
-    return x;
-}
+__device__ __forceinline__ double wsum(double x) { return gsum<64>(x); }
 
 // (a desc, g asc) order of dominant-row candidates
 __device__ __forceinline__ bool better(double a, int g, double b, int h) { return a > b || (a == b && g < h); }
