@@ -24,7 +24,11 @@
 namespace rsai {
 
 namespace {
-constexpr int NT = 256;                    // threads per workgroup
+// Threads per workgroup (one per CU: LDS): a column waits on its own passes over its block, so
+// tall blocks want as many lanes as the registers of a panel allow. 512 against 256: twelve
+// mixed matrices (power-law columns of up to some thousand rows here) 2.47 -> 1.39 ms; 100 x
+// 100 grid, eps = 0.1 (blocks of 100 to 250 rows, which four waves hold) 1.12 -> 1.25 ms.
+constexpr int NT = 512;
 constexpr int NW = NT / 64;                // waves
 constexpr int BLOGH = 14;                  // row hash: 16384 slots
 constexpr int BH = 1 << BLOGH;
@@ -106,6 +110,10 @@ __device__ __forceinline__ void bargmax(double &a, int &g, BigLds &S) {
     __syncthreads();
 }
 
+// Waves that share the rows of an m-row block: half of them where they hold every row, so that
+// the sums over the waves are half as long.
+__device__ __forceinline__ int row_waves(int m) { return m <= NT / 2 ? NW / 2 : NW; }
+
 typedef double mfma_d4 __attribute__((ext_vector_type(4)));
 
 // V(r, i) of the current panel: reflector i (column p0 + i) below its diagonal,
@@ -135,7 +143,8 @@ __device__ void panel_update(double *B, int64_t ld, double *y, int m, int qn, in
     mfma_d4 acc[NCTMAX + 1];
 #pragma unroll
     for (int t = 0; t <= NCTMAX; ++t) acc[t] = mfma_d4{0.0, 0.0, 0.0, 0.0};
-    for (int r0 = p0 + 4 * w; r0 < m; r0 += 4 * NW) {
+    const int nw = row_waves(m);
+    for (int r0 = p0 + 4 * w; r0 < m && w < nw; r0 += 4 * nw) {
         const int r = r0 + lk;
         const double a = vget(B, ld, m, p0, pw, r, li);
         acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, a, acc[0], 0, 0, 0);
@@ -150,7 +159,7 @@ __device__ void panel_update(double *B, int64_t ld, double *y, int m, int qn, in
     }
 #pragma unroll
     for (int t = 0; t <= NCTMAX; ++t)
-        if (t <= nct)
+        if (t <= nct && w < nw)
 #pragma unroll
             for (int e = 0; e < 4; ++e) red[((w * (NCTMAX + 1) + t) * 64 + lane) * 4 + e] = acc[t][e];
     __syncthreads();
@@ -159,7 +168,8 @@ __device__ void panel_update(double *B, int64_t ld, double *y, int m, int qn, in
     for (int x = tid; x < (nct + 1) * 256; x += NT) {
         double v = 0.0;
 #pragma unroll
-        for (int ww = 0; ww < NW; ++ww) v += red[(ww * (NCTMAX + 1)) * 256 + x];
+        for (int ww = 0; ww < NW; ++ww)
+            if (ww < nw) v += red[(ww * (NCTMAX + 1)) * 256 + x];
         red[x] = v;
     }
     __syncthreads();
@@ -228,11 +238,13 @@ __device__ void panel_update(double *B, int64_t ld, double *y, int m, int qn, in
 // turn use BUF 0 and 1, so that each needs one barrier: the other call's lies between a
 // buffer's reads and its next writes.
 template <int LO, int HI, int BUF>
-__device__ __forceinline__ void bsum_many(double (&x)[NB + 1], BigLds &S) {
+__device__ __forceinline__ void bsum_many(double (&x)[NB + 1], int nw, BigLds &S) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (w < nw) {
 #pragma unroll
-    for (int u = LO; u < HI; ++u) x[u] = gsum<64>(x[u]);
-    if (lane == 0)
+        for (int u = LO; u < HI; ++u) x[u] = gsum<64>(x[u]);
+    }
+    if (lane == 0 && w < nw)
 #pragma unroll
         for (int u = LO; u < HI; ++u) S.redp[BUF][w * (NB + 1) + u] = x[u];
     __syncthreads();
@@ -240,7 +252,8 @@ __device__ __forceinline__ void bsum_many(double (&x)[NB + 1], BigLds &S) {
     for (int u = LO; u < HI; ++u) {
         double t = 0.0;
 #pragma unroll
-        for (int ww = 0; ww < NW; ++ww) t += S.redp[BUF][ww * (NB + 1) + u];
+        for (int ww = 0; ww < NW; ++ww)
+            if (ww < nw) t += S.redp[BUF][ww * (NB + 1) + u];
         x[u] = t;
     }
 }
@@ -262,7 +275,7 @@ __device__ __forceinline__ void panel_step(double (&pv)[RPT][NB], int m, int p0,
         if (r >= j && r < m) x[0] += pv[i][UJ] * pv[i][UJ];
         if (r == j) x[1] = pv[i][UJ];
     }
-    bsum_many<0, 2, 0>(x, S);
+    bsum_many<0, 2, 0>(x, row_waves(m), S);
     const double x0 = x[1];
     double nx, be;
     hh_scalars(x[0], x0, nx, be);
@@ -288,7 +301,7 @@ __device__ __forceinline__ void panel_step(double (&pv)[RPT][NB], int m, int p0,
 #pragma unroll
                 for (int i = 0; i < RPT; ++i) d[u] += v[i] * pv[i][u];
             }
-            bsum_many<UJ + 1, NB, 1>(d, S);
+            bsum_many<UJ + 1, NB, 1>(d, row_waves(m), S);
 #pragma unroll
             for (int u = UJ + 1; u < NB; ++u) {
                 const double f = d[u] * be;
@@ -602,8 +615,10 @@ __global__ __launch_bounds__(NT) void big_kernel(BigArgs args) {
                 // with the compact WY form Q_p = I - V T V^T (FP64 MFMA 16x16x4).
                 for (int p0 = q0; p0 < qn; p0 += NB) {
                     const int pw = min(NB, qn - p0);
-                    // blocks of up to 1024 rows: the panel in registers; taller: in the slab
-                    if (m <= NT * 2) {
+                    // blocks of up to 2048 rows: the panel in registers; taller: in the slab
+                    if (m <= NT) {
+                        if (panel_factor_regs<1>(B, ld, m, p0, pw, S)) singular = true;
+                    } else if (m <= NT * 2) {
                         if (panel_factor_regs<2>(B, ld, m, p0, pw, S)) singular = true;
                     } else if (m <= NT * 4) {
                         if (panel_factor_regs<4>(B, ld, m, p0, pw, S)) singular = true;
@@ -678,23 +693,40 @@ __global__ __launch_bounds__(NT) void big_kernel(BigArgs args) {
                 if (singular) { status = ST_SINGULAR; break; }
                 fq = qn;
                 fm = m;
-                // back substitution by wave 0: lane c holds m_c
+                // back substitution by wave 0, column by column: lane i holds (Q^T e)_i and
+                // (Q^T e)_{i+64}; the columns' entries are loaded BS at a time, ahead of
+                // the chain of broadcasts
                 if (tid < 64) {
-                    double mc_lane = 0.0;
-                    for (int j = qn - 1; j >= 0; --j) {
-                        double part = 0.0;
-                        for (int c = j + 1 + tid; c < qn; c += 64)
-                            part += B[(int64_t)c * ld + j] * S.mt[c];
-                        part = gsum<16>(part);
-                        part += __shfl_xor(part, 16);
-                        part += __shfl_xor(part, 32);
-                        const double mj = (y[j] - part) / S.rd[j];
-                        if (tid == 0) S.mt[j] = mj;
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
-                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                        (void)mc_lane;
+                    constexpr int BS = 4;
+                    static_assert(BQMAX_BIG <= 128, "two entries a lane");
+                    double ya = tid < qn ? y[tid] : 0.0, yb = tid + 64 < qn ? y[tid + 64] : 0.0;
+                    const double ra = tid < qn ? S.rd[tid] : 1.0, rb = tid + 64 < qn ? S.rd[tid + 64] : 1.0;
+                    const double ia = 1.0 / ra, ib = 1.0 / rb;
+                    double ma = 0.0, mb = 0.0;
+                    for (int j0 = qn - 1; j0 >= 0; j0 -= BS) {
+                        double ca[BS], cb[BS];
+#pragma unroll
+                        for (int u = 0; u < BS; ++u) {
+                            const int j = j0 - u;
+                            ca[u] = tid < j ? B[(int64_t)j * ld + tid] : 0.0;
+                            cb[u] = tid + 64 < j ? B[(int64_t)j * ld + tid + 64] : 0.0;
+                        }
+#pragma unroll
+                        for (int u = 0; u < BS; ++u) {
+                            const int j = j0 - u;
+                            if (j < 0) break;
+                            const int l = j & 63;
+                            const double mj = j < 64
+                                ? div_by(readlane_f64(ya, l), readlane_f64(ra, l), readlane_f64(ia, l))
+                                : div_by(readlane_f64(yb, l), readlane_f64(rb, l), readlane_f64(ib, l));
+                            if (tid == j) ma = mj;
+                            if (tid + 64 == j) mb = mj;
+                            ya -= ca[u] * mj;
+                            yb -= cb[u] * mj;
+                        }
                     }
+                    if (tid < qn) S.mt[tid] = ma;
+                    if (tid + 64 < qn) S.mt[tid + 64] = mb;
                 }
                 __syncthreads();
                 double s = 0.0;

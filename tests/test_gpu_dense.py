@@ -79,3 +79,20 @@ def test_kept_factors_small_eps():
     gpu["plan"].backward(torch.from_numpy(g).cuda(), 0.7, dA)
     want, scale = oracle.backward(A, gpu["colptr"], gpu["rowidx"], gpu["val"], g, w_frob=0.7, scale=True)
     compare_grad(dA.cpu().numpy(), want, scale, label="dense-factors")
+
+
+@pytest.mark.parametrize("n", [500, 1000, 1900, 3000])
+def test_tall_blocks(n):
+    """Second level: blocks of 40 to 94 columns and up to 512, 1024, 2048 and more rows (the
+    panel in one, two and four register rows a lane, then in memory)."""
+    rng = np.random.default_rng(n)
+    rows, vals = [], []
+    for j in range(n):
+        r = (j + 1 + rng.choice(n - 1, size=65, replace=False)) % n
+        v = rng.standard_normal(65)
+        rows += [j, *r]
+        vals += [1.1 * np.abs(v).sum(), *v]
+    A = gen.from_coo(n, rows, np.repeat(np.arange(n), 66), vals)
+    kw = dict(c=1, lmax=1, eps=0.05, tol=1e-3)
+    ref = oracle.rsai(A, drop=oracle.DROP_NONE, **kw)
+    compare(A, run_gpu(A, drop="none", spill_capacity=n, **kw), ref, label=f"tall-{n}", margin_tol=1e-13)
