@@ -785,10 +785,10 @@ __global__ __launch_bounds__(NT, WPC * NT / 256) void wide_kernel(WideArgs args)
                     // stays (the smaller column index on ties)
                     const bool inq = lane < q;
                     const double am = inq ? fabs(S.mt[lane]) : -1.0;
-                    const int jg = inq ? S.Jl[lane] : INT_MAX;
                     unsigned long long keepm = __ballot(inq && am > th);
                     const int nk = __popcll(keepm);
                     if (nk == 0) {
+                        const int jg = inq ? S.Jl[lane] : INT_MAX;
                         double ba = am;
                         int bg = jg;
 #pragma unroll
@@ -798,6 +798,8 @@ __global__ __launch_bounds__(NT, WPC * NT / 256) void wide_kernel(WideArgs args)
                             if (a2 > ba || (a2 == ba && g2 < bg)) { ba = a2; bg = g2; }
                         }
                         keepm = __ballot(inq && jg == bg);
+                        // (every wave has read J before the first one compacts it)
+                        __syncthreads();
                     }
                     if (nk < q) {
                         // rows of the dropped columns lose one holder; the others keep their
