@@ -1145,6 +1145,8 @@ __global__ __launch_bounds__(NT, WPC * NT / 256) void wide_kernel(WideArgs args)
                     qcap = kargs().rec_alt_cap[d];
                 }
             }
+            // (every wave has read the counters that thread 0 reuses here)
+            __syncthreads();
             if (tid == 0) {
                 int ps = INT_MAX;
                 if (qo) ps = atomicAdd(qc, 1);

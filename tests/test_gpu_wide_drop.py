@@ -1,5 +1,6 @@
-"""Sparse-block class where a drop takes every column but one: values so large that no |m_j|
-passes the tolerance, so each solve keeps the largest alone."""
+"""Sparse-block class where a drop takes every column but one (values so large that no |m_j|
+passes the tolerance, so each solve keeps the largest alone), and where blocks of many shared
+rows are handed over to the dense class."""
 import numpy as np
 import pytest
 
@@ -32,3 +33,20 @@ def test_no_column_passes(n, maxlen, c, lmax, eps, keep):
     assert ((ref["nJmax"] > 1) & (ref["nImax"] > 128)).sum() > 1000
     compare(A, run_gpu(A, drop="fixed", spill_capacity=n, keep_factors=keep, **kw), ref,
             label=f"all-dropped-{n}-{maxlen}", margin_tol=1e-13)
+
+
+@pytest.mark.parametrize("keep", [False, True])
+def test_hand_over_with_many_shared_rows(keep):
+    """Blocks whose shared rows (a few hundred) no level of the class holds go on to the dense
+    class."""
+    rng = np.random.default_rng(5)
+    n = 400
+    d = np.where(rng.random((n, n)) < 0.15, rng.standard_normal((n, n)), 0.0)
+    np.fill_diagonal(d, 0.0)
+    np.fill_diagonal(d, 1.1 * np.abs(d).sum(axis=0))
+    A = gen.from_dense(d)
+    kw = dict(c=1, lmax=1, eps=0.01)
+    ref = oracle.rsai(A, drop=oracle.DROP_NONE, **kw)
+    assert ref["nJmax"].max() <= 128 and ref["nImax"].min() > 256
+    compare(A, run_gpu(A, drop="none", spill_capacity=n, keep_factors=keep, **kw), ref, label="many-shared",
+            margin_tol=1e-13)
