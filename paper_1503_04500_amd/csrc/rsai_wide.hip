@@ -1190,6 +1190,7 @@ __global__ __launch_bounds__(NT, WPC * NT / 256) void wide_kernel(WideArgs args)
                 __syncthreads();
                 continue;
             }
+            __syncthreads();  // (every wave has read its place before the output reuses the counter)
             status = ST_CAP;  // no room in the next class
             if (tid == 0 && qo != nullptr) atomicOr(kargs().err, 32);  // queue full
         }

@@ -1,6 +1,6 @@
 """Sparse-block class where a drop takes every column but one (values so large that no |m_j|
 passes the tolerance, so each solve keeps the largest alone), and where blocks of many shared
-rows are handed over to the dense class."""
+rows are handed over to the dense class, with and without room there."""
 import numpy as np
 import pytest
 
@@ -38,7 +38,8 @@ def test_no_column_passes(n, maxlen, c, lmax, eps, keep):
 @pytest.mark.parametrize("keep", [False, True])
 def test_hand_over_with_many_shared_rows(keep):
     """Blocks whose shared rows (a few hundred) no level of the class holds go on to the dense
-    class."""
+    class; without room in its queue the call says so, and the next one is unaffected."""
+    import paper_1503_04500_amd.rsai as rsai
     rng = np.random.default_rng(5)
     n = 400
     d = np.where(rng.random((n, n)) < 0.15, rng.standard_normal((n, n)), 0.0)
@@ -48,5 +49,7 @@ def test_hand_over_with_many_shared_rows(keep):
     kw = dict(c=1, lmax=1, eps=0.01)
     ref = oracle.rsai(A, drop=oracle.DROP_NONE, **kw)
     assert ref["nJmax"].max() <= 128 and ref["nImax"].min() > 256
+    with pytest.raises(rsai.RSAIError, match="spill_capacity"):
+        rsai.build(rsai.Matrix.from_host(A), drop="none", spill_capacity=8, keep_factors=keep, **kw).nnz()
     compare(A, run_gpu(A, drop="none", spill_capacity=n, keep_factors=keep, **kw), ref, label="many-shared",
             margin_tol=1e-13)
