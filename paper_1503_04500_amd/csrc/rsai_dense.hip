@@ -51,7 +51,7 @@ static_assert(MM + NT < HI, "the row hash holds I and one round of new entries")
 
 struct DLds {
     double R[TILE];            // gather tile; R (column c from c (c - 1) / 2); values by row
-    double part[2][NW][64];    // products of a step, per wave
+    double part[2][NW][64];    // products of a step, per wave; values by row where R is kept
     double piv[2][64];         // row j of the block
     double mt[64], mo[64];     // solution by slot, and in ascending column order
     double rd[64];             // diagonal of R
@@ -637,13 +637,25 @@ __global__ __launch_bounds__(NT, 4) void dense_kernel(DenseArgs args) {
                 S.roff[lane + 64] = h + x1 - n1;
             }
             __syncthreads();
-            // (a block with more entries than the tile holds goes 32 rows at a time)
-            const int rstep = nent <= TILE ? MM : TROWS;
+            // The values' buffer: the gather tile. Where R is kept for the adjoint it has to
+            // outlive this phase (the column may end without another solve): the part of the
+            // tile past R, or the steps' products if they are the larger, hold the values. A
+            // block with more entries than the buffer goes as many rows at a time as fit (a
+            // row has at most q).
+            double *vals = S.R;
+            int vcap = TILE;
+            if (args.out.fac != nullptr) {
+                constexpr int PART = 2 * NW * 64;
+                const int tail = TILE - rcol(q);
+                vals = tail >= PART ? S.R + rcol(q) : &S.part[0][0][0];
+                vcap = tail >= PART ? tail : PART;
+            }
+            const int rstep = nent <= vcap ? MM : min(vcap / q, MM);
             for (int lo = 0; lo < m; lo += rstep) {
                 const int base = S.roff[lo];
                 auto put = [&](int li, int ps, double v) {
                     if (li >= lo && li < lo + rstep)
-                        S.R[S.roff[li] - base + __popcll(S.rmask[li] & ((1ull << ps) - 1ull))] = v;
+                        vals[S.roff[li] - base + __popcll(S.rmask[li] & ((1ull << ps) - 1ull))] = v;
                 };
 #pragma unroll
                 for (int s = 0; s < NE; ++s)
@@ -660,7 +672,7 @@ __global__ __launch_bounds__(NT, 4) void dense_kernel(DenseArgs args) {
                     double acc = 0.0;
                     int at = S.roff[i] - base;
                     for (unsigned long long mk = S.rmask[i]; mk != 0ull; mk &= mk - 1ull)
-                        acc = __fma_rn(S.R[at++], S.mo[__builtin_ctzll(mk)], acc);
+                        acc = __fma_rn(vals[at++], S.mo[__builtin_ctzll(mk)], acc);
                     S.racc[i] = acc - ((i == kidx) ? 1.0 : 0.0);
                 }
                 __syncthreads();
