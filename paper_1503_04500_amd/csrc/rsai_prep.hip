@@ -555,15 +555,17 @@ void launch_scan_i32(const int32_t *in, int64_t n, int64_t *out, int64_t *tmp, h
 // arena slot. One launch forms colptr of M (the exclusive scan of nJ) and compacts the
 // slots: a tile of T columns is scanned by its block (single-pass look-back, as in
 // k_scan1) and then copied, 16 lanes per column, 8 columns in flight. Bound by the
-// look-back chain and the copy's latency. Tiles of 256 columns while all tiles fit eight
-// look-back windows (of 64 tiles), of 1024 beyond: on the 512 x 512 grid 256 tiles of 1024
-// take 19 us, 1024 tiles of 256 32 us (16 windows); on 1024 columns 10.5 and 8.2 us. As
-// two launches (scan, then copy) these were 26.5 and 12.2 us.
+// look-back chain and the copy's latency: small tiles spread few columns over more CUs, large
+// ones shorten the chain. Tiles of 256 columns up to ASM_TILES of them, of 1024 beyond; both
+// measured on grids (build's event times, us, 256 / 1024): n = 1024 10.7 / 12.3, 16384
+// 12.0 / 13.3, 32761 12.9 / 13.8, 40000 13.9 / 14.0, 50625 15.1 / 14.4, 65536 15.9 / 14.9,
+// 131044 22.7 / 16.3, 262144 35.1 / 22.3. As two launches (scan, then copy) the assembly took
+// 26.5 us on 262144 columns and 12.2 on 1024 where one launch took 19.2 and 8.2 (kernel times).
 // state: asm_state_elems(n) zeroed words (k_scan1's layout). The same pass fills the
 // summary the host reads after the build (zeroed at its start): sum[0] = nnz of M,
 // sum[1] = error flags, sum[2..4] = columns with status singular / cap / anything else
 // not ok.
-constexpr int ASM_SMALL = 256, ASM_LARGE = 1024, ASM_WINDOWS = 8 * 64;
+constexpr int ASM_SMALL = 256, ASM_LARGE = 1024, ASM_TILES = 160;
 int64_t asm_state_elems(int64_t n) { return 1 + (n + ASM_SMALL - 1) / ASM_SMALL; }
 
 template <int ASM_T>
@@ -665,7 +667,7 @@ void launch_assemble(int64_t n, int qcap, const int64_t *off, const int32_t *nJ,
         hipLaunchKernelGGL(kernel, dim3((unsigned)((n + t - 1) / t)), dim3((unsigned)t), 0, s, n, qcap, off, nJ, colptrM,
                            arenaJ, arenaV, rowidxM, valM, status, err, state, summary);
     };
-    if (n <= (int64_t)ASM_SMALL * ASM_WINDOWS) go(k_assemble<ASM_SMALL>, ASM_SMALL);
+    if (n <= (int64_t)ASM_SMALL * ASM_TILES) go(k_assemble<ASM_SMALL>, ASM_SMALL);
     else go(k_assemble<ASM_LARGE>, ASM_LARGE);
 }
 

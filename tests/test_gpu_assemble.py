@@ -1,4 +1,4 @@
-"""Assembly of M at the edges of its tiles (256 columns per tile up to 131072 columns, 1024
+"""Assembly of M at the edges of its tiles (256 columns per tile up to 40960 columns, 1024
 beyond; 64 predecessor tiles read at a time): colptr, pattern and values against the
 oracle."""
 import numpy as np
@@ -29,3 +29,9 @@ def test_assembly_tile_edges(n):
     gpu = run_gpu(A, drop="fixed", **kw)
     assert int(gpu["colptr"][-1]) == gpu["rowidx"].size == int(ref["colptr"][-1])
     compare(A, gpu, ref, label=f"assemble-{n}", margin_tol=1e-14)
+
+
+@pytest.mark.parametrize("n", [256 * 160 - 1, 256 * 160, 256 * 160 + 1, 1024 * 64 + 1])
+def test_tile_size_edges(n):
+    """Where the tiles change from 256 to 1024 columns, and past one window of the latter."""
+    test_assembly_tile_edges(n)
