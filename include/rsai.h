@@ -256,8 +256,9 @@ rsai_status rsai_backward(rsai_plan *P, int32_t mat, const double *dM_val, doubl
    (the right-preconditioned form of (1.2)).
    b (input) and x (output) are device arrays of n doubles, distinct; A is the matrix
    the plan was built from (its values as they are now). The scalars of the recurrence
-   stay on the device; the host reads them once per chunk of 4 to 16 iterations, and with
-   use_graph = 1 the chunk is captured once as a HIP graph and replayed. Work buffers
+   stay on the device; the host follows their end flag once per chunk of 6 iterations, with
+   the next chunk queued, and with use_graph = 1 the chunk is captured once as a HIP graph
+   and replayed. Work buffers
    (9 n doubles plus a row-sorted copy of A) come from the allocator and are released
    before return. Host-synchronising.
    On return *iters is the iteration in which the test passed (0 if b = 0 or

@@ -54,10 +54,25 @@ void dev_free(void *p, hipStream_t s) {
     else (void)hipFree(p);
 }
 
+// Words of pinned host memory that kernels leave flags in (16 per thread, kept until the
+// process ends): the CSC check of a build uses word 0, a solve word 8.
+bool pinned_words(int32_t *&host, int32_t *&dev) {
+    thread_local int32_t *word = nullptr;
+    if (!word && hipHostMalloc((void **)&word, 64, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+        word = nullptr;
+        return false;
+    }
+    void *dp = nullptr;
+    if (hipHostGetDevicePointer(&dp, word, 0) != hipSuccess || !dp) return false;
+    host = word;
+    dev = (int32_t *)dp;
+    return true;
+}
+
 // The synchronous CSC check of a build: the kernel after the check copies the flags to
-// a pinned host word (one per thread, with one event per device, both kept until the
-// process ends), and the host waits for them only once the rest of the sequence is
-// queued, so that the queue never runs dry on the host's wait.
+// a pinned host word (one event per thread and device, kept until the process ends), and
+// the host waits for them only once the rest of the sequence is queued, so that the queue
+// never runs dry on the host's wait.
 struct ValCheck {
     bool active = false;
     int32_t *host = nullptr;   // the word (host address)
@@ -67,23 +82,15 @@ struct ValCheck {
 constexpr int32_t kValUnset = -1;
 bool val_check_prepare(ValCheck &vc) {
     constexpr int kMaxDev = 64;
-    thread_local int32_t *word = nullptr;
     thread_local hipEvent_t evs[kMaxDev] = {};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDev) return false;
-    if (!word && hipHostMalloc((void **)&word, 64, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
-        word = nullptr;
-        return false;
-    }
-    void *dp = nullptr;
-    if (hipHostGetDevicePointer(&dp, word, 0) != hipSuccess || !dp) return false;
+    if (!pinned_words(vc.host, vc.dev)) return false;
     if (!evs[dev] && hipEventCreateWithFlags(&evs[dev], hipEventDisableTiming) != hipSuccess) {
         evs[dev] = nullptr;
         return false;
     }
-    *(volatile int32_t *)word = kValUnset;
-    vc.host = word;
-    vc.dev = (int32_t *)dp;
+    *(volatile int32_t *)vc.host = kValUnset;
     vc.ev = evs[dev];
     return true;
 }
@@ -1276,69 +1283,79 @@ static rsai_status bicg_solve(const rsai_csc &A, int mode, const int64_t *mrp, c
     h[0].maxit = h[1].maxit = maxit;
     if (hipMemcpyAsync(a.st, h, sizeof(h), hipMemcpyHostToDevice, s) != hipSuccess)
         return cleanup(fail(RSAI_E_HIP, "state upload failed"));
+    // Iterations are enqueued in chunks, each ending with a settle that leaves the state's done
+    // flag in pinned memory. A chunk is queued before the host waits for the one before it, so
+    // the GPU never idles on the host (28 us a read otherwise, against 26 us of an iteration at
+    // n = 22500); a chunk's own end costs 9 us, and those past the solve's end run as no-ops
+    // (22 us an iteration at n = 100 000, against 57 us of a live one). Chunks of 4 / 6 / 8:
+    // 100 000 power-law columns (23 iterations) 1.89 / 1.90 / 1.95 ms, 300 x 300 grid (202)
+    // 8.35 / 8.17 / 8.17 ms. With a wait for every chunk, of 4 to 16 iterations in two graphs,
+    // these took 1.95 and 8.56 ms; with one graph of 16 iterations the grid took 8.2 ms.
+    constexpr int CHUNK = 6;
+    static_assert(CHUNK % 2 == 0, "a chunk ends on the partial-sum buffer that it began with");
+    int32_t *flag = nullptr;
+    if (!pinned_words(flag, a.host_done)) return cleanup(fail(RSAI_E_HIP, "pinned memory for the solve's state"));
+    flag += 8;
+    a.host_done += 8;
+    *(volatile int32_t *)flag = kValUnset;
     seq.init(s);
-    // iterations are enqueued in chunks, each ending with a settle; the host reads the state
-    // after one chunk, and from 32 iterations on after a quarter of the iterations so far, up
-    // to CHUNK_MAX: an iteration enqueued past the last costs its five launches (22 us against
-    // 57 us of an iteration at n = 100 000), a read about 15 us. A power-law matrix of 100 000
-    // columns, 18 iterations: read every 16, 1757 us; now 1555 us.
-    constexpr int CHUNK = 4, CHUNK_MAX = 16;
-    hipGraphExec_t gx[2] = {};  // CHUNK iterations, CHUNK_MAX iterations (long solves)
+    hipGraphExec_t gx = nullptr;
     hipStream_t cs = nullptr;
-    auto capture = [&](int count, hipGraphExec_t &exec) {
+    hipEvent_t ev[2] = {};
+    auto release = [&]() {  // (once nothing of it runs any more)
+        (void)hipStreamSynchronize(s);
+        if (gx) (void)hipGraphExecDestroy(gx);
+        if (cs) (void)hipStreamDestroy(cs);
+        for (hipEvent_t e : ev)
+            if (e) (void)hipEventDestroy(e);
+    };
+    for (hipEvent_t &e : ev)
+        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+            release();
+            return cleanup(fail(RSAI_E_HIP, "hipEventCreate failed"));
+        }
+    if (use_graph) {
         hipGraph_t g = nullptr;
-        bool ok = (cs || hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) == hipSuccess) &&
+        bool ok = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) == hipSuccess &&
                   hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) == hipSuccess;
         if (ok) {
-            seq.iterations(count, cs);
+            seq.iterations(CHUNK, cs);
             seq.settle(cs);
             ok = hipStreamEndCapture(cs, &g) == hipSuccess && g;
         }
-        if (ok) ok = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0) == hipSuccess;
+        if (ok) ok = hipGraphInstantiate(&gx, g, nullptr, nullptr, 0) == hipSuccess;
         if (g) (void)hipGraphDestroy(g);
-        return ok;
-    };
-    auto drop_graphs = [&]() {
-        for (hipGraphExec_t g : gx)
-            if (g) (void)hipGraphExecDestroy(g);
-        if (cs) (void)hipStreamDestroy(cs);
-    };
-    if (use_graph && !capture(CHUNK, gx[0])) {
-        drop_graphs();
-        return cleanup(fail(RSAI_E_HIP, "graph capture of the iteration failed"));
+        if (!ok) {
+            release();
+            return cleanup(fail(RSAI_E_HIP, "graph capture of the iteration failed"));
+        }
     }
-    int done_iters = 0;
     hipError_t he = hipSuccess;
     bool stuck = false;
     BicgState hs{};
-    for (;;) {
-        he = hipMemcpyAsync(&hs, a.st, sizeof(hs), hipMemcpyDeviceToHost, s);
-        if (he == hipSuccess) he = hipStreamSynchronize(s);
-        if (he != hipSuccess || hs.done) break;
-        const int chunk = std::min(std::max(done_iters / 4 / CHUNK, 1) * CHUNK, CHUNK_MAX);
+    for (int64_t c = 0;; ++c) {
         if (use_graph) {
-            if (chunk == CHUNK_MAX && !gx[1] && !capture(CHUNK_MAX, gx[1])) {
-                drop_graphs();
-                return cleanup(fail(RSAI_E_HIP, "graph capture of the iteration failed"));
-            }
-            if (chunk == CHUNK_MAX) he = hipGraphLaunch(gx[1], s);
-            else
-                for (int c = 0; c < chunk && he == hipSuccess; c += CHUNK) he = hipGraphLaunch(gx[0], s);
+            he = hipGraphLaunch(gx, s);
         } else {
-            seq.iterations(chunk, s);
+            seq.iterations(CHUNK, s);
             seq.settle(s);
             he = hipGetLastError();
         }
+        if (he == hipSuccess) he = hipEventRecord(ev[c & 1], s);
+        if (he == hipSuccess && c > 0) he = hipEventSynchronize(ev[(c - 1) & 1]);
         if (he != hipSuccess) break;
-        done_iters += chunk;
-        if (done_iters > maxit + 2 * CHUNK_MAX) {  // every iteration advances or ends the solve
+        // (unset until the first settle's store has arrived)
+        if (c > 0 && *(volatile int32_t *)flag > 0) break;
+        if (c * CHUNK > (int64_t)maxit + 32) {  // every iteration advances or ends the solve
             stuck = true;
             break;
         }
     }
-    drop_graphs();
-    if (stuck) return cleanup(fail(RSAI_E_STATE, "BiCGStab state did not advance"));
+    if (he == hipSuccess) he = hipMemcpyAsync(&hs, a.st, sizeof(hs), hipMemcpyDeviceToHost, s);
+    if (he == hipSuccess) he = hipStreamSynchronize(s);
+    release();
     if (he != hipSuccess) return cleanup(fail(RSAI_E_HIP, "BiCGStab iteration failed: %s", hipGetErrorString(he)));
+    if (stuck && !hs.done) return cleanup(fail(RSAI_E_STATE, "BiCGStab state did not advance"));
     if (hs.half && hipMemcpyAsync(x, a.xh, 8 * n, hipMemcpyDeviceToDevice, s) != hipSuccess)
         return cleanup(fail(RSAI_E_HIP, "copy of the half-step solution failed"));
     *iters = hs.ret;

@@ -201,6 +201,7 @@ struct BicgArgs {
     double *x, *r, *rh, *p, *w, *v, *s, *t, *xh, *res, *fr, *fp, *fs;
     double *part;        // 2 buffers of 2 * BICG_MAXGRID partial sums
     BicgState *st;       // 2 copies of the state
+    int32_t *host_done;  // the state's done flag as of the last settle (pinned host memory)
 };
 struct BicgStep {
     int stage;             // partial sums to fold in first (0: none)

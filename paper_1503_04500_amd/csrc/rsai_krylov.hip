@@ -215,11 +215,15 @@ __global__ __launch_bounds__(KT) void kb_init(BicgArgs a, BicgStep q) {
     write_partials<2>(acc, q.pout);
 }
 
-// one workgroup: fold in pending partial sums and write the state to both copies
+// one workgroup: fold in pending partial sums, write the state to both copies and its done
+// flag to the host's word
 __global__ __launch_bounds__(KT) void kb_settle(BicgArgs a, BicgStep q, BicgState *other) {
     BicgState S;
     take_state(q, S);
-    if (threadIdx.x == 0) *other = S;
+    if (threadIdx.x == 0) {
+        *other = S;
+        __hip_atomic_store(a.host_done, S.done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 // [beta] p = r + beta w, fp = F r + beta F w (F r kept), res = b - A x | ||res||^2
