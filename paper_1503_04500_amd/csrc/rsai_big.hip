@@ -1,4 +1,4 @@
-// Second level of the dense class of the RSAI(tol) build: one 256-thread workgroup per
+// Second level of the dense class of the RSAI(tol) build: one 512-thread workgroup per
 // column, for the columns that outgrow the first level (rsai_dense.hip): LS blocks
 // A(I_k, J_k) of up to BMMAX rows and BQMAX columns, e.g. the power-law matrices whose
 // long columns bring hundreds to thousands of rows into I_k.
@@ -234,9 +234,9 @@ __device__ void panel_update(double *B, int64_t ld, double *y, int m, int qn, in
 }
 
 // Block-wide sums of x[LO..HI) (up to NB + 1 values): a wave-level tree per value,
-// then the four waves' partials through LDS. Every thread gets the totals. Two calls in
-// turn use BUF 0 and 1, so that each needs one barrier: the other call's lies between a
-// buffer's reads and its next writes.
+// then the partials of the nw waves that hold rows through LDS. Every thread gets the
+// totals. Two calls in turn use BUF 0 and 1, so that each needs one barrier: the other
+// call's lies between a buffer's reads and its next writes.
 template <int LO, int HI, int BUF>
 __device__ __forceinline__ void bsum_many(double (&x)[NB + 1], int nw, BigLds &S) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;

@@ -506,7 +506,7 @@ __device__ __forceinline__ int hfind(const int *hk, int key) {
 }
 
 // Ranks of the keys key[0..N) among the n keys of an LDS list (16-byte aligned, followed
-// by three entries of INT_MAX): four keys per read, the reads independent.
+// by at least three entries of INT_MAX): four keys per read, the reads independent.
 template <int N>
 __device__ __forceinline__ void ranks_in(const int *list, int n, const int (&key)[N], int (&rank)[N]) {
 #pragma unroll

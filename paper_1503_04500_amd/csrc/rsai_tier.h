@@ -115,7 +115,7 @@ struct alignas(16) GLds {
     int cb[CP + 1];           // first entry of the column in each slot of J (CSC of A; nnz < 2^31)
     int cl[CP + 1];           // its length
     int Ilist[C::MMAX + 1];
-    alignas(16) int Jlist[C::QMAX + 4];  // (three entries of INT_MAX after the last column)
+    alignas(16) int Jlist[C::QMAX + 4];  // (INT_MAX in the four entries after the last column)
     int hI[C::HSI + 1];
     int hJ[C::HSJ + 1];
     int Rh[CMAX];             // pending dominant rows
