@@ -26,7 +26,7 @@
 // wave can do alone take no workgroup barrier; and the compressed solve eliminates the columns
 // of one shared row in closed form. 400 000 power-law columns (2 to 200 entries), c = 3,
 // eps = 0.4: a wave per column, every entry looked up again per phase and all columns stepped
-// through, 15.6 ms in levels 0 to 3; now 9.4 ms.
+// through, 15.6 ms in levels 0 to 3; now 9.1 ms.
 //
 // Columns arrive as spill records of the previous class. A column whose |I_k| or
 // compressed block outgrows this class moves on to the next one.
