@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from paper_1503_04500_amd import gen
-from tests.parity import run_gpu
+from tests.parity import compare_grad, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -29,3 +29,19 @@ def test_same_bits(name, drop):
     plain, kept = run_gpu(A, **kw), run_gpu(A, keep_factors=True, **kw)
     for key in ("colptr", "rowidx", "val", "resnorm", "loops", "nI", "nJ", "status"):
         assert np.array_equal(plain[key], kept[key]), f"{name}-{drop}: {key}"
+
+
+@pytest.mark.parametrize("name", sorted(MATRICES))
+def test_adjoint_on_the_kept_factors(name):
+    """R of every column's final pattern, whatever way its solves took: entry by entry against
+    the oracle's adjoint on the same pattern."""
+    import torch
+
+    import oracle
+    A, kw = MATRICES[name]()
+    gpu = run_gpu(A, drop="fixed", tol=1e-3, spill_capacity=A.n, keep_factors=True, **kw)
+    g = np.random.default_rng(1).standard_normal(gpu["val"].size)
+    dA = torch.zeros(A.nnz, dtype=torch.float64, device="cuda")
+    gpu["plan"].backward(torch.from_numpy(g).cuda(), 0.7, dA)
+    want, scale = oracle.backward(A, gpu["colptr"], gpu["rowidx"], gpu["val"], g, w_frob=0.7, scale=True)
+    compare_grad(dA.cpu().numpy(), want, scale, label=f"kept-{name}")
